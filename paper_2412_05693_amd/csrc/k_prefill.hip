@@ -18,16 +18,14 @@
 //   sweep 2 (S = Q K^T orientation: one key per lane) -- recompute the logits,
 //            P = exp2(z - m - log2 l) exactly, and sum over the rows held in
 //            the lane's registers, so each lane ends with one key's column sum.
-// Both sweeps are software-pipelined: the MFMAs of tile t+1's logits are issued
-// before tile t's softmax, so the matrix cores and the VALU work overlap within
-// a wave.
 //
-// Key tiles hold 64 rows from one source: the unit's cache rows [0, len0) first,
-// then the block's input rows.  Tiles are copied global -> LDS by buffer loads
-// that write LDS directly (no staging registers); rows past a source's range
-// come back as zeros.  LDS rows are padded (the DMA writes zeros into the
-// padding slots), so the MFMA operand reads are free of bank conflicts and use
-// base + immediate addressing.
+// Key tiles hold 64 rows from one source: whole tiles of the unit's cache rows
+// [0, len0) first, then the block's input rows, then the cache's last rows if
+// they do not fill a tile.  Tiles are copied global -> LDS by buffer loads
+// that write LDS directly (no staging registers), tile t + 1's while tile t is
+// worked on; rows past a source's range come back as zeros.  The 16-byte chunks of an LDS row are stored in an order
+// that depends on the row (the copies read their source chunks in that order),
+// so the MFMA operand reads are free of bank conflicts without padding.
 // K rows of a 32-key sub-tile sit in LDS row order kappa (bits 2 and 3 of the
 // row swapped), which makes the register layout of the S^T accumulator equal
 // to the PV MFMA's B operand; V reaches the PV MFMA through gfx950's
@@ -52,8 +50,6 @@ constexpr float kNegInf = -__builtin_huge_valf();
 constexpr float kPosInf = __builtin_huge_valf();
 constexpr int kRsrcWord3 = 0x00020000;
 constexpr float kRescaleLog2 = 8.0f;
-// s_waitcnt with vmcnt(0) and the other counters left alone
-constexpr int kWaitVm0 = 0x0F70;
 
 // ---- prefill timeline (measurement builds: BM_PREFILL_TIMELINE) ----
 // Thread 0 of each workgroup keeps the fields of include/bm_probe.h in
@@ -111,12 +107,9 @@ struct Cfg {
   using qfrag_t = typename std::conditional<BF16, bf16x8, float>::type;
   static constexpr int RB = D * (int)sizeof(E);          // bytes per K/V row
   static constexpr int CPR = RB / 16;                     // 16-byte chunks per row
-  // LDS rows are padded by one (K) or two (V) 16-byte chunks: the MFMA operand
-  // reads of K (16 lanes, 16 rows, one chunk each) and the transposing reads of
-  // V (4 rows x 32 bytes per 16-lane group) then fall in distinct banks.
-  static constexpr int KCP = CPR + 1, VCP = CPR + 2;     // chunks per padded row
-  static constexpr int KSTRIDE = KCP * 16, VSTRIDE = VCP * 16;
-  static constexpr int K_BYTES = kKeyTile * KSTRIDE, V_BYTES = kKeyTile * VSTRIDE;
+  static constexpr int TILE_BYTES = kKeyTile * RB;        // one K or V tile in LDS
+  static constexpr int RPS = 1024 / RB;                   // rows per 1 KB copy
+  static constexpr int NCOPY = TILE_BYTES / 1024 / kWaves;   // copies per wave and tile
   static constexpr int QSTEPS = BF16 ? D / 16 : D / 2;   // MFMA K-steps over d
   static constexpr int MT = D / 32;                       // 32-row M-tiles of O^T
 };
@@ -132,19 +125,38 @@ __device__ __forceinline__ f32x16 mfma_step(typename Cfg<BF16, D>::qfrag_t a,
   }
 }
 
-// fragment of LDS row `row` of a K tile for K-step kk, lane half h.  bf16:
-// K-step kk contracts the 16-byte chunks 2 kk (lane half 0) and 2 kk + 1 (lane
-// half 1) of d, so the two halves of a query row's load fall in one cache line
+// LDS rows are stored without padding; chunk c of row r sits at position
+// c ^ swz(r) of its row, which spreads the chunks that one read instruction
+// touches over the banks (a 256-byte line of them holds 256 / RB rows):
+// K and output rows: 16 rows, the same chunk of each; V: rows 4 i .. 4 i + 3,
+// the same 64 bytes of each.
 template <bool BF16, int D>
-__device__ __forceinline__ typename Cfg<BF16, D>::qfrag_t k_frag(const char* ks, int row, int h,
-                                                                 int kk) {
+__device__ __forceinline__ constexpr int swz_k(int r) {
   using C = Cfg<BF16, D>;
+  return C::RB >= 256 ? r & 15 : (r >> 1) & 7;
+}
+template <bool BF16, int D>
+__device__ __forceinline__ constexpr int swz_v(int r) {
+  using C = Cfg<BF16, D>;
+  return !BF16 ? 0 : C::RB >= 256 ? (r & 3) << 2 : ((r >> 1) & 1) << 2;
+}
+
+// Address in a K tile of the fragment of row n (and, 32 rows on, of row n + 32)
+// for K-step kk, lane half h, from frag0 = k_frag0(n, h).  bf16: K-step kk
+// contracts the 16-byte chunks 2 kk (lane half 0) and 2 kk + 1 (lane half 1) of
+// d, so the two halves of a query row's load fall in one cache line
+template <bool BF16, int D>
+__device__ __forceinline__ int k_frag0(int n, int h) {
+  using C = Cfg<BF16, D>;
+  const int c = BF16 ? h : h * (C::CPR / 2);
+  return n * C::RB + (c ^ swz_k<BF16, D>(n)) * 16;
+}
+template <bool BF16, int D>
+__device__ __forceinline__ typename Cfg<BF16, D>::qfrag_t k_frag(const char* ks, int frag0, int kk) {
   if constexpr (BF16) {
-    const int b = (2 * kk + h) * 16;
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + row * C::KSTRIDE + b));
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + (frag0 ^ (32 * kk))));
   } else {
-    const int b = (h * (D / 2) + kk) * 4;
-    return *reinterpret_cast<const float*>(ks + row * C::KSTRIDE + b);
+    return *reinterpret_cast<const float*>(ks + (frag0 ^ (16 * (kk >> 2))) + 4 * (kk & 3));
   }
 }
 
@@ -157,7 +169,9 @@ struct Geo {
   bool qvalid;
   bool wave_active;
   int in_rows;     // block rows the workgroup reads: min(n_tok, pbase + PT)
-  int ntc, nt;     // cache tiles, all tiles
+  int ncf, nbt;    // whole cache tiles, block tiles
+  int nt;          // all tiles: whole cache tiles, block tiles, a partial cache tile
+  int nun;         // the first nun tiles need no mask in this wave
   int pad;         // left pad tokens of the sample (positions < pad are pads)
   bool qpad;       // this lane's query row is a pad token
 };
@@ -175,7 +189,9 @@ __device__ __forceinline__ Geo make_geo(const PrefillArgs& a) {
   s.pt = lin - s.u * a.npt_used;
   s.bi = s.u / a.n_kv_heads;
   s.hk = s.u - s.bi * a.n_kv_heads;
-  s.w = threadIdx.x >> 6;
+  // the wave's number in a scalar register: what follows from it (rows, heads,
+  // which tiles are masked) is then scalar work and scalar branches
+  s.w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   s.lane = threadIdx.x & 63;
   s.n = s.lane & 31;
   s.h = s.lane >> 5;
@@ -189,8 +205,10 @@ __device__ __forceinline__ Geo make_geo(const PrefillArgs& a) {
   s.wave_active = s.wrow0 < a.n_tok;
   s.wlast = min(a.n_tok - 1, s.wrow0 + kRowsPerWave - 1);
   s.in_rows = min(a.n_tok, s.pbase + PT);
-  s.ntc = (a.len0 + kKeyTile - 1) / kKeyTile;
-  s.nt = s.ntc + (s.in_rows + kKeyTile - 1) / kKeyTile;
+  s.ncf = a.len0 / kKeyTile;
+  s.nbt = (s.in_rows + kKeyTile - 1) / kKeyTile;
+  s.nt = s.ncf + s.nbt + (a.len0 % kKeyTile != 0);
+  s.nun = s.wave_active ? s.ncf + (s.wrow0 + 1) / kKeyTile : 0;
   s.pad = PAD ? max(0, a.pad[s.bi]) : 0;
   s.qpad = a.t0 + s.row < s.pad;
   return s;
@@ -206,54 +224,55 @@ struct TileInfo {
 
 __device__ __forceinline__ TileInfo tile_info(const PrefillArgs& a, const Geo& s, int t) {
   TileInfo ti;
-  ti.cache = t < s.ntc;
-  ti.base = (ti.cache ? t : t - s.ntc) * kKeyTile;
+  const bool block = t >= s.ncf && t < s.ncf + s.nbt;
+  ti.cache = !block;
+  ti.base = (block ? t - s.ncf : min(t, s.ncf)) * kKeyTile;
   ti.slot0 = ti.cache ? ti.base : a.len0 + ti.base;
   ti.valid = min(kKeyTile, (ti.cache ? a.len0 : s.in_rows) - ti.base);
   return ti;
 }
 
-// does the wave see any key of tile t; does the tile need masking for it
+// does the wave see any key of the tile
 __device__ __forceinline__ bool tile_active(const Geo& s, const TileInfo& ti) {
   return s.wave_active && (ti.cache || ti.base <= s.wlast);
 }
-__device__ __forceinline__ bool tile_masked(const Geo& s, const TileInfo& ti) {
-  return ti.cache ? ti.valid < kKeyTile : ti.base + kKeyTile - 1 > s.wrow0;
-}
 
 // Tiles of K (rows in kappa order) and V are copied into LDS with buffer loads
-// that write LDS directly; lane i of instruction j of wave w fills the 16-byte
-// chunk (w * DMA_PER_WAVE + j) * 64 + i of the tile.  The buffer resource of a
-// tile's source (cache rows [0, len0) or the block rows the workgroup reads) is
-// built per tile from values forced into scalar registers, so the loads take
-// it straight from SGPRs.
-struct TileSrc {
-  __amdgpu_buffer_rsrc_t rsrc;
-};
-
-// An out-of-range offset: the lane writes zeros (used for the padding slots).
-constexpr int kOutOfRange = 0x7FFFFFF0;
-
-// Copy one tile into padded LDS rows.  Slot g = 64 * seg + lane of the tile
-// holds chunk g % CP of row g / CP; chunks >= CPR are padding.  K rows are
-// stored in kappa order within each 32-row sub-tile.
+// that write LDS directly: copy j of wave w fills the 1 KB (RPS rows) numbered
+// w + kWaves j of the tile, lane i its 16-byte chunk i.  The buffer resource
+// starts at the tile's first source row and ends at the last row that exists
+// (rows past it arrive as zeros); both come from scalar registers.
 template <bool BF16, int D, bool K>
-__device__ __forceinline__ void dma_rows(char* dst, const TileSrc& src, const TileInfo& ti,
-                                         const Geo& s) {
+__device__ __forceinline__ int copy_offset(const Geo& s, int j) {
   using C = Cfg<BF16, D>;
-  constexpr int CP = K ? C::KCP : C::VCP;   // also the number of 1 KB segments
-#pragma unroll
-  for (int j = 0; j < (CP + kWaves - 1) / kWaves; ++j) {
-    const int seg = s.w + kWaves * j;
-    if (seg < CP) {   // uniform per wave
-      const int g = seg * 64 + s.lane;
-      const int r = g / CP, c = g - r * CP;
-      const int key = K ? (r & ~31) + kappa(r & 31) : r;
-      const int off = c < C::CPR ? (ti.base + key) * C::RB + c * 16 : kOutOfRange;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(src.rsrc, (lds_void*)(dst + seg * 1024), 16, off, 0, 0, 0);
-    }
-  }
+  const int r = (s.w + kWaves * j) * C::RPS + s.lane / C::CPR, p = s.lane % C::CPR;
+  const int src = K ? (r & ~31) + kappa(r & 31) : r;
+  return src * C::RB + (p ^ (K ? swz_k<BF16, D>(r) : swz_v<BF16, D>(r))) * 16;
 }
+
+// One 1 KB copy, lane i's 16 bytes at offset `off` of the resource to LDS byte
+// `lds` + 16 i.  Written as assembly so that the compiler does not order the
+// tile reads behind the copies in flight (it cannot tell the buffers apart once
+// their choice is a run-time value): tile_fence() waits for a wave's copies, and
+// the barrier behind it for everyone's.
+__device__ __forceinline__ void copy_1k(u32x4 rsrc, int off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+               ::"v"(off), "s"(rsrc), "s"(lds) : "m0");
+}
+
+// off: this lane's copy_offset(s, 0).  A copy stride of 16 or more rows leaves
+// kappa and the swizzles as they are, so copy j reads 4096 j bytes further on.
+template <bool BF16, int D, bool K>
+__device__ __forceinline__ void copy_tile(uint32_t dst, u32x4 rsrc, int off, const Geo& s) {
+  using C = Cfg<BF16, D>;
+#pragma unroll
+  for (int j = 0; j < C::NCOPY; ++j)
+    copy_1k(rsrc, kWaves * C::RPS >= 16 ? off + 4096 * j : copy_offset<BF16, D, K>(s, j),
+            dst + (s.w + kWaves * j) * 1024);
+}
+
+// wait for the wave's copies; LDS may hold new tiles from here on
+__device__ __forceinline__ void tile_fence() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 template <bool BF16, int D, int G, bool PAD>
 __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_attn_kernel(PrefillArgs a) {
@@ -262,20 +281,17 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   using C = Cfg<BF16, D>;
   using E = typename C::E;
   constexpr int RB = C::RB;
-  // separate arrays per buffer: with the ping-pong index known at compile time
-  // the compiler can tell the tile being filled from the tile being read
-  __shared__ __attribute__((aligned(1024))) char kb0[C::K_BYTES];
-  __shared__ __attribute__((aligned(1024))) char kb1[C::K_BYTES];
-  __shared__ __attribute__((aligned(1024))) char vb0[C::V_BYTES];
-  __shared__ __attribute__((aligned(1024))) char vb1[C::V_BYTES];
-  __shared__ float cs0[kWaves][kKeyTile];
-  __shared__ float cs1[kWaves][kKeyTile];
+  // two K and two V tile buffers; parity t & 1 of tile t in sweep 1, (nt + t) & 1
+  // in sweep 2
+  __shared__ __attribute__((aligned(1024))) char kv[4 * C::TILE_BYTES];
+  char* const kbuf = kv;
+  char* const vbuf = kv + 2 * C::TILE_BYTES;
+  __shared__ float cs[2][kWaves][kKeyTile];
   // positions of the cached keys of tile t in pk_ring[t % 3] (left padding
-  // only): tile t's positions are read while tile t + 2's are being fetched
+  // only): a wave may still read tile t's when tile t + 1's are being fetched
   __shared__ int32_t pk_ring[3][kKeyTile];
   // the block's last query's weights per wave (TOVA's key), double-buffered like cs
-  __shared__ float lws0[kWaves][kKeyTile];
-  __shared__ float lws1[kWaves][kKeyTile];
+  __shared__ float lws[2][kWaves][kKeyTile];
   uint64_t tl[BM_TIMELINE_FIELDS] = {};
   if constexpr (kTimeline) tl[BM_TL_ENTRY] = tl_now();
   const Geo s = make_geo<G, PAD>(a);
@@ -298,13 +314,13 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   auto wait_and_sync = [&](int f_wait, int f_barrier) __device__ {
     if constexpr (kTimeline) {
       const uint64_t a0 = tl_now();
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      tile_fence();
       const uint64_t a1 = tl_now();
       __syncthreads();
       tl[f_wait] += a1 - a0;
       tl[f_barrier] += tl_now() - a1;
     } else {
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      tile_fence();
       __syncthreads();
     }
   };
@@ -356,27 +372,26 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   const uint64_t vc_base = (uint64_t)(static_cast<const E*>(a.vc) + (int64_t)s.u * a.cap * D);
   const uint64_t ki_base = (uint64_t)(static_cast<const E*>(a.kin) + plane * D);
   const uint64_t vi_base = (uint64_t)(static_cast<const E*>(a.vin) + plane * D);
+  auto rsrc_of = [&](uint64_t p, int bytes) __device__ {
+    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)p),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(p >> 32)) & 0xFFFFu,
+                 (uint32_t)__builtin_amdgcn_readfirstlane(bytes), (uint32_t)kRsrcWord3};
+  };
   auto tile_src = [&](const TileInfo& ti, bool kside) __device__ {
     const uint64_t p = ti.cache ? (kside ? kc_base : vc_base) : (kside ? ki_base : vi_base);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-    const int nrec = __builtin_amdgcn_readfirstlane((ti.cache ? a.len0 : s.in_rows) * RB);
-    TileSrc r;
-    r.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, nrec, kRsrcWord3);
-    return r;
+    return rsrc_of(p + (uint64_t)(ti.base * RB), ((ti.cache ? a.len0 : s.in_rows) - ti.base) * RB);
   };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)kv;
+  const int koff = copy_offset<BF16, D, true>(s, 0), voff = copy_offset<BF16, D, false>(s, 0);
   const uint64_t pos_base = (uint64_t)(a.pos + (int64_t)s.u * a.cap);
-  auto dma_k = [&](char* dst, const TileInfo& ti, int t) __device__ {
-    dma_rows<BF16, D, true>(dst, tile_src(ti, true), ti, s);
+  auto dma_k = [&](int par, const TileInfo& ti, int t) __device__ {
+    copy_tile<BF16, D, true>(lds0 + par * C::TILE_BYTES, tile_src(ti, true), koff, s);
     if (PAD && s.pad > 0 && ti.cache && s.w == 0) {
       // the tile's key positions, in key order, next to the K rows
-      const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)pos_base);
-      const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(pos_base >> 32));
-      const int nrec = __builtin_amdgcn_readfirstlane(a.len0 * 4);
-      const __amdgpu_buffer_rsrc_t r =
-          __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, nrec, kRsrcWord3);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)pk_ring[t % 3], 4,
-                                               (ti.base + s.lane) * 4, 0, 0, 0);
+      const u32x4 r = rsrc_of(pos_base, a.len0 * 4);
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
+                   ::"v"((ti.base + s.lane) * 4), "s"(r),
+                   "s"((uint32_t)(uintptr_t)(lds_void*)pk_ring[t % 3]) : "m0");
     }
   };
   // bit k set: key k of tile ti is a pad token (cache keys through the LDS copy
@@ -387,8 +402,8 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     const int n = min(max(s.pad - a.t0 - ti.base, 0), kKeyTile);
     return n >= 64 ? ~0ull : ((1ull << n) - 1);
   };
-  auto dma_v = [&](char* dst, const TileInfo& ti) __device__ {
-    dma_rows<BF16, D, false>(dst, tile_src(ti, false), ti, s);
+  auto dma_v = [&](int par, const TileInfo& ti) __device__ {
+    copy_tile<BF16, D, false>(lds0 + (2 + par) * C::TILE_BYTES, tile_src(ti, false), voff, s);
   };
 
   // ---- query fragments: lane (n, h) holds row n; bf16: the d-chunks 2 kk + h
@@ -418,18 +433,21 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 
   // logits of one tile: S^T (one query per lane) or S (one key per lane); the
   // K fragments of step kk + 1 are read while the MFMAs of step kk run
+  const int frag0 = k_frag0<BF16, D>(s.n, s.h);
   auto qk_tile = [&](auto st_tag, const char* ks, f32x16* acc) __device__ {
     constexpr bool ST = decltype(st_tag)::value;
+    int f0 = frag0;
+    asm volatile("" : "+v"(f0));   // the swizzled addresses are formed here, not kept
     acc[0] = f32x16{};
     acc[1] = f32x16{};
     typename C::qfrag_t kf[2][2];
-    kf[0][0] = k_frag<BF16, D>(ks, s.n, s.h, 0);
-    kf[0][1] = k_frag<BF16, D>(ks, 32 + s.n, s.h, 0);
+    kf[0][0] = k_frag<BF16, D>(ks, f0, 0);
+    kf[0][1] = k_frag<BF16, D>(ks + 32 * RB, f0, 0);
 #pragma unroll
     for (int kk = 0; kk < C::QSTEPS; ++kk) {
       if (kk + 1 < C::QSTEPS) {
-        kf[(kk + 1) & 1][0] = k_frag<BF16, D>(ks, s.n, s.h, kk + 1);
-        kf[(kk + 1) & 1][1] = k_frag<BF16, D>(ks, 32 + s.n, s.h, kk + 1);
+        kf[(kk + 1) & 1][0] = k_frag<BF16, D>(ks, f0, kk + 1);
+        kf[(kk + 1) & 1][1] = k_frag<BF16, D>(ks + 32 * RB, f0, kk + 1);
       }
 #pragma unroll
       for (int st = 0; st < 2; ++st)
@@ -474,12 +492,14 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     constexpr bool MASK = decltype(mask_tag)::value;
     if constexpr (MASK) {
       // key k of the tile is visible iff k <= lim_k
-      const int lim_k = ti.cache ? ti.valid - 1 : qrow - ti.base;
+      // (the lane half's 8 h comes off the limit, so each key compares against
+      // a constant and no register holds its index)
+      const int lim_k = (ti.cache ? ti.valid - 1 : qrow - ti.base) - 8 * s.h;
 #pragma unroll
       for (int st = 0; st < 2; ++st)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          sacc[st][r] = st_key(st, r >> 2, r & 3, s.h) <= lim_k ? sacc[st][r] : kNegInf;
+          sacc[st][r] = st_key(st, r >> 2, r & 3, 0) <= lim_k ? sacc[st][r] : kNegInf;
     }
     // tile max on the raw logits (the scale is positive), then one fma per exp2
     float tmax = kNegInf;
@@ -524,16 +544,19 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
       // and receives V[key0 + 0..3][d0 + i].
       const int j16 = s.lane & 15, dhalf = (s.lane >> 4) & 1;
       const int vrow = 8 * s.h + (j16 >> 2);
-      const int vb = (16 * dhalf + 4 * (j16 & 3)) * 2;
+      int vbase = vrow * RB + 16 * swz_v<BF16, D>(vrow) + (16 * dhalf + 4 * (j16 & 3)) * 2;
+      asm volatile("" : "+v"(vbase));
       // the 2 x MT transposing reads of K-step ks4 + 1 are issued before the
       // MFMAs of step ks4
       u32x4 vf[2][C::MT];
       auto vload = [&](int ks4, u32x4* dst) __device__ {
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt) {
-          const int r0 = 16 * ks4 + vrow, b = vb + 64 * mt;
-          const bf16v4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)(vs + r0 * C::VSTRIDE + b));
-          const bf16v4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)(vs + (r0 + 4) * C::VSTRIDE + b));
+          // (the swizzle of a row depends on row % 4 alone; rows of 16 ks4 and
+          // 4 further on have the same)
+          const char* p = vs + (vbase ^ (64 * mt)) + 16 * ks4 * RB;
+          const bf16v4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)p);
+          const bf16v4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)(p + 4 * RB));
           const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
           dst[mt] = u32x4{l2.x, l2.y, h2.x, h2.y};
         }
@@ -562,71 +585,52 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
           const int key = st_key(st, r >> 2, r & 3, s.h);
 #pragma unroll
           for (int mt = 0; mt < C::MT; ++mt) {
-            const float vv = *reinterpret_cast<const float*>(vs + key * C::VSTRIDE + (32 * mt + s.n) * 4);
+            const float vv = *reinterpret_cast<const float*>(vs + key * RB + (32 * mt + s.n) * 4);
             oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, sacc[st][r], oacc[mt], 0, 0, 0);
           }
         }
     }
   };
 
-  // prologue: K(0), V(0), K(1) land in LDS; logits of tile 0
-  dma_k(kb0, tile_info(a, s, 0), 0);
-  dma_v(vb0, tile_info(a, s, 0));
-  if (nt > 1) dma_k(kb1, tile_info(a, s, 1), 1);
+  // prologue: K(0) and V(0) land in LDS
+  dma_k(0, tile_info(a, s, 0), 0);
+  dma_v(0, tile_info(a, s, 0));
   stamp(BM_TL_COPIES_ISSUED);
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  tile_fence();
   append_store();
   __syncthreads();
   stamp(BM_TL_FIRST_TILE);
-  // logits ping-pong between two register sets; the loop is unrolled by two so
-  // every buffer choice below is a compile-time constant
-  f32x16 sa[2], sb[2];
-  // sweep 2's first K tiles are fetched during sweep 1's last iteration (not
-  // with left padding: that iteration still reads the position ring slots the
-  // early copies would refill)
-  const bool early_k2 = !PAD && a.accumulate;
-  if (tile_active(s, tile_info(a, s, 0))) qk_st(kb0, sa);
-  __syncthreads();   // every wave has read K(0) before iteration 0 refills its buffer
-  // iteration t (parity P = t & 1): K(t+1) and V(t) are in LDS and `cur` holds
-  // tile t's logits; K(t+2) and V(t+1) are fetched meanwhile
-  auto sweep1_iter = [&](auto par, int t, f32x16* cur, f32x16* nxt) __device__ {
-    constexpr int P = decltype(par)::value;
-    char* k_fill = P == 0 ? kb0 : kb1;
-    char* k_next = P == 0 ? kb1 : kb0;
-    char* v_cur = P == 0 ? vb0 : vb1;
-    char* v_fill = P == 0 ? vb1 : vb0;
-    const int32_t* pk_cur = pk_ring[t % 3];       // positions of tile t
+  f32x16 sl[2];
+  // tile t: K(t) and V(t) are in LDS; K(t+1) and V(t+1) are fetched meanwhile
+  auto sweep1_step = [&](auto mask_tag, int t) __device__ {
+    const int par = t & 1;
     const TileInfo ti = tile_info(a, s, t);
     const uint64_t issue0 = tl_now();
-    if (t + 2 < nt) dma_k(k_fill, tile_info(a, s, t + 2), t + 2);
     if (t + 1 < nt) {
       const TileInfo tn = tile_info(a, s, t + 1);
-      dma_v(v_fill, tn);
-      if constexpr (kTimeline) tl[BM_TL_S1_COPY_ISSUE] += tl_now() - issue0;
-      if (tile_active(s, tn)) qk_st(k_next, nxt);
+      dma_k(par ^ 1, tn, t + 1);
+      dma_v(par ^ 1, tn);
+    } else if (a.accumulate) {
+      // sweep 2's first K tile (its position ring slot: nobody reads tile
+      // nt - 3's any more)
+      dma_k(par ^ 1, tile_info(a, s, 0), nt);
     }
-    if (early_k2 && t == nt - 1) {
-      // both K buffers are free in the last iteration: fetch the first two K
-      // tiles of sweep 2 now, so they land with this iteration's wait
-      dma_k(kb0, tile_info(a, s, 0), 0);
-      if (nt > 1) dma_k(kb1, tile_info(a, s, 1), 1);
-    }
-    if (tile_active(s, ti)) {
+    if constexpr (kTimeline) tl[BM_TL_S1_COPY_ISSUE] += tl_now() - issue0;
+    if (!decltype(mask_tag)::value || tile_active(s, ti)) {
+      qk_st(kbuf + par * C::TILE_BYTES, sl);
       if constexpr (PAD) {
-        const uint64_t padk = pad_bits(ti, pk_cur);
-        if (padk) hide_pads(cur, padk);
+        const uint64_t padk = pad_bits(ti, pk_ring[t % 3]);
+        if (padk) hide_pads(sl, padk);
       }
-      if (tile_masked(s, ti))
-        sweep1_tile(std::true_type{}, cur, v_cur, ti);
-      else
-        sweep1_tile(std::false_type{}, cur, v_cur, ti);
+      sweep1_tile(mask_tag, sl, vbuf + par * C::TILE_BYTES, ti);
     }
     wait_and_sync(BM_TL_S1_WAIT, BM_TL_S1_BARRIER);
   };
-  for (int t = 0; t < nt; t += 2) {
-    sweep1_iter(std::integral_constant<int, 0>{}, t, sa, sb);
-    if (t + 1 < nt) sweep1_iter(std::integral_constant<int, 1>{}, t + 1, sb, sa);
-  }
+  // two loops, so that the common one holds no second path (a masked and an
+  // unmasked tile behind a branch made the compiler keep the accumulators twice)
+  int t1 = 0;
+  for (; t1 < s.nun; ++t1) sweep1_step(std::false_type{}, t1);
+  for (; t1 < nt; ++t1) sweep1_step(std::true_type{}, t1);
   stamp(BM_TL_SWEEP1_END);
 
   // ---- finish rows: normalise, store O, row log-sum-exp (log2 units) ----
@@ -640,13 +644,11 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     if constexpr (BF16) {
       // The wave's 32 output rows are contiguous in memory (one head, 32
       // consecutive positions).  They go through LDS -- the V buffers are
-      // idle once sweep 1 is over; each wave uses its own padded 32-row
-      // region -- so the stores are whole 1 KB runs instead of 16 bytes per
-      // row per instruction.
-      constexpr int OSTRIDE = C::KSTRIDE;   // padded row: D * 2 + 16 bytes
-      static_assert(kWaves == 4 && 2 * kRowsPerWave * OSTRIDE <= C::V_BYTES,
-                    "two waves' rows per V buffer");
-      char* ost = (s.w < 2 ? vb0 : vb1) + (s.w & 1) * (kRowsPerWave * OSTRIDE);
+      // idle once sweep 1 is over; each wave uses its own 32-row region (rows
+      // swizzled like K's) -- so the stores are whole 1 KB runs instead of 16
+      // bytes per row per instruction.
+      static_assert(kWaves * kRowsPerWave * RB == 2 * C::TILE_BYTES, "the waves' rows fill the V buffers");
+      char* ost = vbuf + s.w * (kRowsPerWave * RB);
 #pragma unroll
       for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll
@@ -654,7 +656,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
           const int d0 = 32 * mt + 8 * i + 4 * s.h;
           const u32x2 w = {pack_bf16x2(oacc[mt][4 * i + 0] * sc, oacc[mt][4 * i + 1] * sc),
                            pack_bf16x2(oacc[mt][4 * i + 2] * sc, oacc[mt][4 * i + 3] * sc)};
-          *reinterpret_cast<u32x2*>(ost + s.n * OSTRIDE + d0 * 2) = w;
+          *reinterpret_cast<u32x2*>(ost + s.n * RB + ((d0 * 2) ^ (16 * swz_k<BF16, D>(s.n)))) = w;
         }
       // the output row's address is computed here rather than kept from the
       // query load (which would hold two registers through both sweeps)
@@ -666,7 +668,8 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 #pragma unroll
       for (int j = 0; j < RUNS; ++j) {
         const int r = RPR * j + s.lane / (RB / 16), c = s.lane % (RB / 16);
-        const u32x4 v = *reinterpret_cast<const u32x4*>(ost + r * OSTRIDE + c * 16);
+        const u32x4 v =
+            *reinterpret_cast<const u32x4*>(ost + r * RB + 16 * (c ^ swz_k<BF16, D>(r)));
         if (s.wrow0 + r < a.n_tok)
           *reinterpret_cast<u32x4*>(o + (int64_t)r * RB + c * 16) = v;
       }
@@ -732,54 +735,35 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     }
   };
 
-  // prologue: K(0), K(1) land in LDS (already there when sweep 1's last
-  // iteration fetched them); logits of tile 0
-  if (!early_k2) {
-    dma_k(kb0, tile_info(a, s, 0), 0);
-    if (nt > 1) dma_k(kb1, tile_info(a, s, 1), 1);
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    __syncthreads();
-  }
-  if (tile_active(s, tile_info(a, s, 0))) qk_s(kb0, sa);
-  __syncthreads();   // every wave has read K(0) before iteration 0 refills its buffer
   stamp(BM_TL_SWEEP2_START);
-  // iteration t (parity P = t & 1): K(t+1) is in LDS and `cur` holds tile t's logits
-  auto sweep2_iter = [&](auto par, int t, f32x16* cur, f32x16* nxt) __device__ {
-    constexpr int P = decltype(par)::value;
-    char* k_fill = P == 0 ? kb0 : kb1;
-    char* k_next = P == 0 ? kb1 : kb0;
-    float (*cs)[kKeyTile] = P == 0 ? cs0 : cs1;
-    float (*lws)[kKeyTile] = P == 0 ? lws0 : lws1;
-    const int32_t* pk_cur = pk_ring[t % 3];
+  // tile t: K(t) is in LDS (sweep 1's last step fetched K(0)); K(t+1) is
+  // fetched meanwhile
+  auto sweep2_step = [&](auto mask_tag, int t) __device__ {
+    const int par = (nt + t) & 1;
     const TileInfo ti = tile_info(a, s, t);
-    if (t + 2 < nt) dma_k(k_fill, tile_info(a, s, t + 2), t + 2);
-    if (t + 1 < nt) {
-      const TileInfo tn = tile_info(a, s, t + 1);
-      if (tile_active(s, tn)) qk_s(k_next, nxt);
-    }
-    if (tile_active(s, ti)) {
-      if (tile_masked(s, ti))
-        sweep2_tile(std::true_type{}, cur, ti, cs);
-      else
-        sweep2_tile(std::false_type{}, cur, ti, cs);
+    f32x16* cur = sl;
+    if (t + 1 < nt) dma_k(par ^ 1, tile_info(a, s, t + 1), nt + t + 1);
+    if (!decltype(mask_tag)::value || tile_active(s, ti)) {
+      qk_s(kbuf + par * C::TILE_BYTES, cur);
+      sweep2_tile(mask_tag, cur, ti, cs[par]);
       if constexpr (PAD) {
         // a pad key is visible to no real row (pad rows add nothing: lse = +inf)
-        const uint64_t padk = pad_bits(ti, pk_cur);
+        const uint64_t padk = pad_bits(ti, pk_ring[(nt + t) % 3]);
         if (padk && s.h == 0) {
 #pragma unroll
           for (int st = 0; st < 2; ++st) {
             const int key = 32 * st + kappa(s.n);
-            if ((padk >> key) & 1) cs[s.w][key] = 0.0f;
+            if ((padk >> key) & 1) cs[par][s.w][key] = 0.0f;
           }
         }
       }
     } else if (s.lane < 32) {
-      cs[s.w][s.lane] = 0.0f;
-      cs[s.w][32 + s.lane] = 0.0f;
+      cs[par][s.w][s.lane] = 0.0f;
+      cs[par][s.w][32 + s.lane] = 0.0f;
     }
     if (wg_last) {
       // the last row sees every key of the tile (pads aside)
-      const uint64_t padk = PAD ? pad_bits(ti, pk_cur) : 0;
+      const uint64_t padk = PAD ? pad_bits(ti, pk_ring[(nt + t) % 3]) : 0;
 #pragma unroll
       for (int st = 0; st < 2; ++st) {
         const int key = 32 * st + kappa(s.n);
@@ -792,27 +776,26 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
           v = xhalf_sum(v);
           if (PAD && ((padk >> key) & 1)) v = 0.0f;
         }
-        if (s.h == 0) lws[s.w][key] = v;
+        if (s.h == 0) lws[par][s.w][key] = v;
       }
     }
     wait_and_sync(BM_TL_S2_WAIT, BM_TL_S2_BARRIER);
     if (tid < ti.valid) {
       float acc = 0.0f;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) acc += cs[w][tid];
+      for (int w = 0; w < kWaves; ++w) acc += cs[par][w][tid];
       partial[ti.slot0 + tid] = acc;
       if (wg_last) {
         float lw = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) lw += lws[w][tid];
+        for (int w = 0; w < kWaves; ++w) lw += lws[par][w][tid];
         a.lastw[(int64_t)s.u * a.cap + ti.slot0 + tid] = lw;
       }
     }
   };
-  for (int t = 0; t < nt; t += 2) {
-    sweep2_iter(std::integral_constant<int, 0>{}, t, sa, sb);
-    if (t + 1 < nt) sweep2_iter(std::integral_constant<int, 1>{}, t + 1, sb, sa);
-  }
+  int t2 = 0;
+  for (; t2 < s.nun; ++t2) sweep2_step(std::false_type{}, t2);
+  for (; t2 < nt; ++t2) sweep2_step(std::true_type{}, t2);
   timeline_end();
 }
 
