@@ -19,9 +19,8 @@
 //            P = exp2(z - m - log2 l) exactly, and sum over the rows held in
 //            the lane's registers, so each lane ends with one key's column sum.
 //
-// Key tiles hold 64 rows from one source: whole tiles of the unit's cache rows
-// [0, len0) first, then the block's input rows, then the cache's last rows if
-// they do not fill a tile.  Tiles are copied global -> LDS by buffer loads
+// Key tiles hold 64 rows from one source: the unit's cache rows [0, len0) first,
+// then the block's input rows.  Tiles are copied global -> LDS by buffer loads
 // that write LDS directly (no staging registers), tile t + 1's while tile t is
 // worked on; rows past a source's range come back as zeros.  The 16-byte chunks of an LDS row are stored in an order
 // that depends on the row (the copies read their source chunks in that order),
@@ -45,6 +44,11 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __bf16 __attribute__((vector_size(8))) bf16v4;   // operand type of the LDS transpose read
 typedef __attribute__((address_space(3))) bf16v4 lds_bf16v4;
 typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+// the LDS object at byte `off` (an address kept as a number, so that it takes
+// one register and an immediate offset)
+template <typename T>
+__device__ __forceinline__ T* lds_at(uint32_t off) { return (T*)off; }
 
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr float kPosInf = __builtin_huge_valf();
@@ -170,8 +174,9 @@ struct Geo {
   bool wave_active;
   int in_rows;     // block rows the workgroup reads: min(n_tok, pbase + PT)
   int ncf, nbt;    // whole cache tiles, block tiles
-  int nt;          // all tiles: whole cache tiles, block tiles, a partial cache tile
-  int nun;         // the first nun tiles need no mask in this wave
+  int part;        // 1 if a partial cache tile follows the whole ones
+  int nt;          // all tiles
+  int nbu;         // block tiles that need no mask in this wave
   int pad;         // left pad tokens of the sample (positions < pad are pads)
   bool qpad;       // this lane's query row is a pad token
 };
@@ -207,14 +212,15 @@ __device__ __forceinline__ Geo make_geo(const PrefillArgs& a) {
   s.in_rows = min(a.n_tok, s.pbase + PT);
   s.ncf = a.len0 / kKeyTile;
   s.nbt = (s.in_rows + kKeyTile - 1) / kKeyTile;
-  s.nt = s.ncf + s.nbt + (a.len0 % kKeyTile != 0);
-  s.nun = s.wave_active ? s.ncf + (s.wrow0 + 1) / kKeyTile : 0;
+  s.part = a.len0 % kKeyTile != 0;
+  s.nt = s.ncf + s.part + s.nbt;
+  s.nbu = (s.wrow0 + 1) / kKeyTile;
   s.pad = PAD ? max(0, a.pad[s.bi]) : 0;
   s.qpad = a.t0 + s.row < s.pad;
   return s;
 }
 
-// Where tile t comes from and which of its rows exist.
+// Where a tile comes from and which of its rows exist.
 struct TileInfo {
   bool cache;      // rows from the unit's cache (else the block's input rows)
   int base;        // first source row of the tile
@@ -222,14 +228,20 @@ struct TileInfo {
   int valid;       // rows of the tile that exist
 };
 
+// tile t of sweep 1: the cache's rows in order, then the block's
 __device__ __forceinline__ TileInfo tile_info(const PrefillArgs& a, const Geo& s, int t) {
   TileInfo ti;
-  const bool block = t >= s.ncf && t < s.ncf + s.nbt;
-  ti.cache = !block;
-  ti.base = (block ? t - s.ncf : min(t, s.ncf)) * kKeyTile;
+  const int ntc = s.ncf + s.part;
+  ti.cache = t < ntc;
+  ti.base = (ti.cache ? t : t - ntc) * kKeyTile;
   ti.slot0 = ti.cache ? ti.base : a.len0 + ti.base;
   ti.valid = min(kKeyTile, (ti.cache ? a.len0 : s.in_rows) - ti.base);
   return ti;
+}
+// tile t of sweep 2, whose sums do not depend on the order: a partial cache tile
+// comes last, so that the tiles without a mask are in one run
+__device__ __forceinline__ TileInfo tile_info2(const PrefillArgs& a, const Geo& s, int t) {
+  return tile_info(a, s, t < s.ncf ? t : t == s.nt - 1 && s.part ? s.ncf : t + s.part);
 }
 
 // does the wave see any key of the tile
@@ -238,37 +250,49 @@ __device__ __forceinline__ bool tile_active(const Geo& s, const TileInfo& ti) {
 }
 
 // Tiles of K (rows in kappa order) and V are copied into LDS with buffer loads
-// that write LDS directly: copy j of wave w fills the 1 KB (RPS rows) numbered
-// w + kWaves j of the tile, lane i its 16-byte chunk i.  The buffer resource
-// starts at the tile's first source row and ends at the last row that exists
-// (rows past it arrive as zeros); both come from scalar registers.
+// that write LDS directly: wave w fills the NCOPY consecutive 1 KB pieces (RPS
+// rows each) from NCOPY w on, lane i the 16-byte chunk i of each.  An
+// instruction's immediate offset moves its LDS address and its source address
+// alike, so up to four copies share one LDS base (the M0 register, whose change
+// would have to wait for the copy before it) and a lane's source offset of copy j
+// has the immediate taken off; kBias keeps it from going below zero.  The buffer
+// resource starts kBias bytes before the tile's first source row and ends at the
+// last row that exists (rows past it arrive as zeros); both come from scalar
+// registers.
+constexpr int kBias = 3072;
+
 template <bool BF16, int D, bool K>
 __device__ __forceinline__ int copy_offset(const Geo& s, int j) {
   using C = Cfg<BF16, D>;
-  const int r = (s.w + kWaves * j) * C::RPS + s.lane / C::CPR, p = s.lane % C::CPR;
+  const int r = (s.w * C::NCOPY + j) * C::RPS + s.lane / C::CPR, p = s.lane % C::CPR;
   const int src = K ? (r & ~31) + kappa(r & 31) : r;
-  return src * C::RB + (p ^ (K ? swz_k<BF16, D>(r) : swz_v<BF16, D>(r))) * 16;
+  return src * C::RB + (p ^ (K ? swz_k<BF16, D>(r) : swz_v<BF16, D>(r))) * 16 + kBias - 1024 * (j & 3);
 }
 
-// One 1 KB copy, lane i's 16 bytes at offset `off` of the resource to LDS byte
-// `lds` + 16 i.  Written as assembly so that the compiler does not order the
-// tile reads behind the copies in flight (it cannot tell the buffers apart once
-// their choice is a run-time value): tile_fence() waits for a wave's copies, and
-// the barrier behind it for everyone's.
-__device__ __forceinline__ void copy_1k(u32x4 rsrc, int off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               ::"v"(off), "s"(rsrc), "s"(lds) : "m0");
-}
-
-// off: this lane's copy_offset(s, 0).  A copy stride of 16 or more rows leaves
-// kappa and the swizzles as they are, so copy j reads 4096 j bytes further on.
-template <bool BF16, int D, bool K>
-__device__ __forceinline__ void copy_tile(uint32_t dst, u32x4 rsrc, int off, const Geo& s) {
-  using C = Cfg<BF16, D>;
+// The wave's copies of one tile into the LDS tile at `dst`.  Written as assembly
+// so that the compiler does not order the tile reads behind the copies in flight
+// (it cannot tell the buffers apart once their choice is a run-time value):
+// tile_fence() waits for a wave's copies, and the barrier behind it for everyone's.
+template <int NCOPY>
+__device__ __forceinline__ void copy_tile(uint32_t dst, u32x4 rsrc, const int (&off)[NCOPY], int w) {
+  static_assert(NCOPY % 4 == 0 || NCOPY == 2, "copies per wave and tile");
+  const uint32_t lds = __builtin_amdgcn_readfirstlane(dst + w * (NCOPY * 1024));
+  if constexpr (NCOPY == 2) {
+    asm volatile(
+        "s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds\n\t"
+        "buffer_load_dwordx4 %1, %2, 0 offen offset:1024 lds"
+        ::"v"(off[0]), "v"(off[1]), "s"(rsrc), "s"(lds) : "m0");
+  } else {
 #pragma unroll
-  for (int j = 0; j < C::NCOPY; ++j)
-    copy_1k(rsrc, kWaves * C::RPS >= 16 ? off + 4096 * j : copy_offset<BF16, D, K>(s, j),
-            dst + (s.w + kWaves * j) * 1024);
+    for (int j = 0; j < NCOPY; j += 4)
+      asm volatile(
+          "s_mov_b32 m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
+          "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
+          "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
+          "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
+          ::"v"(off[j]), "v"(off[j + 1]), "v"(off[j + 2]), "v"(off[j + 3]), "s"(rsrc),
+          "s"(__builtin_amdgcn_readfirstlane(lds + 1024 * j)) : "m0");
+  }
 }
 
 // wait for the wave's copies; LDS may hold new tiles from here on
@@ -281,17 +305,19 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   using C = Cfg<BF16, D>;
   using E = typename C::E;
   constexpr int RB = C::RB;
+  // tiles that need no mask go through the interleaved loops
+  constexpr bool FAST = BF16 && !PAD;
   // two K and two V tile buffers; parity t & 1 of tile t in sweep 1, (nt + t) & 1
   // in sweep 2
   __shared__ __attribute__((aligned(1024))) char kv[4 * C::TILE_BYTES];
   char* const kbuf = kv;
   char* const vbuf = kv + 2 * C::TILE_BYTES;
-  __shared__ float cs[2][kWaves][kKeyTile];
+  __shared__ float cs[3][kWaves][kKeyTile];
   // positions of the cached keys of tile t in pk_ring[t % 3] (left padding
   // only): a wave may still read tile t's when tile t + 1's are being fetched
   __shared__ int32_t pk_ring[3][kKeyTile];
-  // the block's last query's weights per wave (TOVA's key), double-buffered like cs
-  __shared__ float lws[2][kWaves][kKeyTile];
+  // the block's last query's weights per wave (TOVA's key)
+  __shared__ float lws[3][kWaves][kKeyTile];
   uint64_t tl[BM_TIMELINE_FIELDS] = {};
   if constexpr (kTimeline) tl[BM_TL_ENTRY] = tl_now();
   const Geo s = make_geo<G, PAD>(a);
@@ -379,19 +405,26 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   };
   auto tile_src = [&](const TileInfo& ti, bool kside) __device__ {
     const uint64_t p = ti.cache ? (kside ? kc_base : vc_base) : (kside ? ki_base : vi_base);
-    return rsrc_of(p + (uint64_t)(ti.base * RB), ((ti.cache ? a.len0 : s.in_rows) - ti.base) * RB);
+    return rsrc_of(p + (uint64_t)(ti.base * RB) - kBias,
+                   ((ti.cache ? a.len0 : s.in_rows) - ti.base) * RB + kBias);
   };
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)kv;
-  const int koff = copy_offset<BF16, D, true>(s, 0), voff = copy_offset<BF16, D, false>(s, 0);
+  int koff[C::NCOPY], voff[C::NCOPY];
+#pragma unroll
+  for (int j = 0; j < C::NCOPY; ++j) {
+    koff[j] = copy_offset<BF16, D, true>(s, j);
+    voff[j] = copy_offset<BF16, D, false>(s, j);
+  }
   const uint64_t pos_base = (uint64_t)(a.pos + (int64_t)s.u * a.cap);
   auto dma_k = [&](int par, const TileInfo& ti, int t) __device__ {
-    copy_tile<BF16, D, true>(lds0 + par * C::TILE_BYTES, tile_src(ti, true), koff, s);
+    copy_tile(lds0 + par * C::TILE_BYTES, tile_src(ti, true), koff, s.w);
     if (PAD && s.pad > 0 && ti.cache && s.w == 0) {
       // the tile's key positions, in key order, next to the K rows
       const u32x4 r = rsrc_of(pos_base, a.len0 * 4);
       asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
                    ::"v"((ti.base + s.lane) * 4), "s"(r),
-                   "s"((uint32_t)(uintptr_t)(lds_void*)pk_ring[t % 3]) : "m0");
+                   "s"(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)pk_ring[t % 3]))
+                   : "m0");
     }
   };
   // bit k set: key k of tile ti is a pad token (cache keys through the LDS copy
@@ -403,7 +436,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     return n >= 64 ? ~0ull : ((1ull << n) - 1);
   };
   auto dma_v = [&](int par, const TileInfo& ti) __device__ {
-    copy_tile<BF16, D, false>(lds0 + (2 + par) * C::TILE_BYTES, tile_src(ti, false), voff, s);
+    copy_tile(lds0 + (2 + par) * C::TILE_BYTES, tile_src(ti, false), voff, s.w);
   };
 
   // ---- query fragments: lane (n, h) holds row n; bf16: the d-chunks 2 kk + h
@@ -475,7 +508,6 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   for (int mt = 0; mt < C::MT; ++mt) oacc[mt] = f32x16{};
   float m_run = kNegInf, l_run = 0.0f;
 
-  // softmax of tile t (S^T in sacc) and O^T += V^T P^T
   // left padding: a real query row sees no pad key (a pad row keeps its causal
   // keys; its output and score contributions are dropped later).  The lane's
   // keys all have bit 3 equal to h, so the pad bits are shifted once.
@@ -488,8 +520,52 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
         if ((hide >> st_key(st, r >> 2, r & 3, 0)) & 1) sacc[st][r] = kNegInf;
   };
 
-  auto sweep1_tile = [&](auto mask_tag, f32x16* sacc, const char* vs, const TileInfo& ti) __device__ {
+  // logits and P of the tile in work.  bf16: P packed, half by half, as the PV
+  // MFMA's B operand; fp32: P replaces the logits in sl
+  f32x16 sl[2];
+  u32x4 pp[2][2];
+  auto pack_p = [&](int half) __device__ {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        pp[half][q][i] = pack_bf16x2(sl[half][8 * q + 2 * i], sl[half][8 * q + 2 * i + 1]);
+  };
+  // The reference m_run moves only when some row of the wave sees a logit more
+  // than kRescaleLog2 above it: the probabilities stay below 2^kRescaleLog2
+  // (exact in fp32, fine in bf16) and the O rescale is rare.
+  auto raise_max = [&](float tmax) __device__ {
+    if (__ballot(tmax * c2 > m_run + kRescaleLog2) != 0) {
+      const float m_new = fmaxf(m_run, tmax * c2);
+      // (a padded row that has seen no key yet keeps m = -inf: nothing to scale)
+      const float alpha = PAD && m_new == kNegInf ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+      l_run *= alpha;
+      m_run = m_new;
+#pragma unroll
+      for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[mt][r] *= alpha;
+    }
+  };
+  auto exp_tile = [&](float m_sub) __device__ {
+    float psum = 0.0f;
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sl[st][r], c2, -m_sub));
+        sl[st][r] = p;
+        psum += p;
+      }
+    l_run += psum;
+    if constexpr (BF16) {
+      pack_p(0);
+      pack_p(1);
+    }
+  };
+  auto softmax_tile = [&](auto mask_tag, const TileInfo& ti) __device__ {
     constexpr bool MASK = decltype(mask_tag)::value;
+    f32x16* sacc = sl;
     if constexpr (MASK) {
       // key k of the tile is visible iff k <= lim_k
       // (the lane half's 8 h comes off the limit, so each key compares against
@@ -507,75 +583,48 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sacc[st][r]);
-    tmax = xhalf_max(tmax);
-    // The reference m_run moves only when some row of the wave sees a logit
-    // more than kRescaleLog2 above it: the probabilities stay below
-    // 2^kRescaleLog2 (exact in fp32, fine in bf16) and the O rescale is rare.
-    if (__ballot(tmax * c2 > m_run + kRescaleLog2) != 0) {
-      const float m_new = fmaxf(m_run, tmax * c2);
-      // (a padded row that has seen no key yet keeps m = -inf: nothing to scale)
-      const float alpha = PAD && m_new == kNegInf ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-      l_run *= alpha;
-      m_run = m_new;
-#pragma unroll
-      for (int mt = 0; mt < C::MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[mt][r] *= alpha;
-    }
-    float psum = 0.0f;
+    raise_max(xhalf_max(tmax));
     // with left padding a row's first tiles can be all pad keys: m_run is still
     // -inf there and every logit is -inf, so subtract 0 to get p = 0, not NaN
     // (without padding every row sees a key in its first tile)
-    const float m_sub = PAD && m_run == kNegInf ? 0.0f : m_run;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(sacc[st][r], c2, -m_sub));
-        sacc[st][r] = p;
-        psum += p;
-      }
-    l_run += psum;
+    exp_tile(PAD && m_run == kNegInf ? 0.0f : m_run);
+  };
+
+  // A operand (V^T) of the PV MFMA: lane (n, h) needs V[key][32 mt + n] for the
+  // 8 keys 16 ks4 + 8 h + e of P's k-slots.  The LDS transpose load gives lane i
+  // of a 16-lane group column i of the 4 x 16 block formed by the group's lanes
+  // 4r..4r+3 (row r), so lane 4r + c points at V[key0 + r][d0 + 4c] and receives
+  // V[key0 + 0..3][d0 + i].  (The swizzle of a row depends on row % 4 alone;
+  // rows of 16 ks4 and 4 further on have the same.)
+  const int j16 = s.lane & 15, dhalf = (s.lane >> 4) & 1;
+  const int vrow = 8 * s.h + (j16 >> 2);
+  const int vbase = vrow * RB + 16 * swz_v<BF16, D>(vrow) + (16 * dhalf + 4 * (j16 & 3)) * 2;
+  auto v_frag = [&](const char* vs, int vb, int ks4, int mt) __device__ {
+    const char* p = vs + (vb ^ (64 * mt)) + 16 * ks4 * RB;
+    const bf16v4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)p);
+    const bf16v4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)(p + 4 * RB));
+    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+    return u32x4{l2.x, l2.y, h2.x, h2.y};
+  };
+  // O^T += V^T P^T of one tile
+  auto pv_tile = [&](const char* vs) __device__ {
     if constexpr (BF16) {
-      // A operand (V^T): lane (n, h) needs V[key][32 mt + n] for the 8 keys
-      // 16 ks + 8 h + e of P's k-slots.  The LDS transpose load gives lane i of
-      // a 16-lane group column i of the 4 x 16 block formed by the group's
-      // lanes 4r..4r+3 (row r), so lane 4r + c points at V[key0 + r][d0 + 4c]
-      // and receives V[key0 + 0..3][d0 + i].
-      const int j16 = s.lane & 15, dhalf = (s.lane >> 4) & 1;
-      const int vrow = 8 * s.h + (j16 >> 2);
-      int vbase = vrow * RB + 16 * swz_v<BF16, D>(vrow) + (16 * dhalf + 4 * (j16 & 3)) * 2;
-      asm volatile("" : "+v"(vbase));
-      // the 2 x MT transposing reads of K-step ks4 + 1 are issued before the
-      // MFMAs of step ks4
+      int vb = vbase;
+      asm volatile("" : "+v"(vb));
+      // the reads of K-step ks4 + 1 are issued before the MFMAs of step ks4
       u32x4 vf[2][C::MT];
-      auto vload = [&](int ks4, u32x4* dst) __device__ {
 #pragma unroll
-        for (int mt = 0; mt < C::MT; ++mt) {
-          // (the swizzle of a row depends on row % 4 alone; rows of 16 ks4 and
-          // 4 further on have the same)
-          const char* p = vs + (vbase ^ (64 * mt)) + 16 * ks4 * RB;
-          const bf16v4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)p);
-          const bf16v4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)(p + 4 * RB));
-          const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-          dst[mt] = u32x4{l2.x, l2.y, h2.x, h2.y};
-        }
-      };
-      vload(0, vf[0]);
+      for (int mt = 0; mt < C::MT; ++mt) vf[0][mt] = v_frag(vs, vb, 0, mt);
 #pragma unroll
       for (int ks4 = 0; ks4 < 4; ++ks4) {
-        if (ks4 + 1 < 4) vload(ks4 + 1, vf[(ks4 + 1) & 1]);
-        const int st = ks4 >> 1, half = ks4 & 1;
-        u32x4 pw;
-        pw.x = pack_bf16x2(sacc[st][8 * half + 0], sacc[st][8 * half + 1]);
-        pw.y = pack_bf16x2(sacc[st][8 * half + 2], sacc[st][8 * half + 3]);
-        pw.z = pack_bf16x2(sacc[st][8 * half + 4], sacc[st][8 * half + 5]);
-        pw.w = pack_bf16x2(sacc[st][8 * half + 6], sacc[st][8 * half + 7]);
-        const bf16x8 pb = __builtin_bit_cast(bf16x8, pw);
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt)
-          oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[ks4 & 1][mt]), pb,
-                                                              oacc[mt], 0, 0, 0);
+          if (ks4 + 1 < 4) vf[(ks4 + 1) & 1][mt] = v_frag(vs, vb, ks4 + 1, mt);
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt)
+          oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8, vf[ks4 & 1][mt]),
+              __builtin_bit_cast(bf16x8, pp[ks4 >> 1][ks4 & 1]), oacc[mt], 0, 0, 0);
       }
     } else {
 #pragma unroll
@@ -586,51 +635,199 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 #pragma unroll
           for (int mt = 0; mt < C::MT; ++mt) {
             const float vv = *reinterpret_cast<const float*>(vs + key * RB + (32 * mt + s.n) * 4);
-            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, sacc[st][r], oacc[mt], 0, 0, 0);
+            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, sl[st][r], oacc[mt], 0, 0, 0);
           }
         }
     }
   };
 
-  // prologue: K(0) and V(0) land in LDS
+  // One step of the interleaved loop: QK^T of tile t (into zn), the softmax of
+  // tile t - 1 (zo, whose running maximum is settled) and its PV product.
+  // What bounds it: per tile and wave 1024 cycles of MFMA, ~750 of VALU work and
+  // 500 of LDS reads; two waves per SIMD cover each other's phases only in part
+  // (one wave: 2550 cycles a tile with the phases one after the other, 2200 like
+  // this; two waves: 3700 and 3300 a round), and at full load on real data the
+  // card holds the clock near 2.0 of 2.4 GHz.  So the order is pinned, MFMA by
+  // MFMA: the QK MFMAs with 24 of a lane's 32 logits between them, then the PV
+  // MFMAs with the last 8 and the maximum of zn.  VALU work is staged over three
+  // places (x = logit - reference, e = exp2, sum and pack), so that no
+  // instruction waits for the one before it; operand reads go out kAhead MFMAs
+  // early.  Sums keep the order of exp_tile.  Per prompt, with the copies' shared
+  // LDS base: full cache b=4 s=8192 2702 -> 2582 us, b=1 s=4096 556 -> 528 us,
+  // b=256 s=2048 (power-bound) 2% faster.
+  auto interleaved_step = [&](f32x16 (&zn)[2], const f32x16 (&zo)[2], uint32_t (&ka)[C::QSTEPS],
+                              uint32_t (&va)[C::MT]) __device__ {
+    if constexpr (FAST) {
+      constexpr int NI = C::QSTEPS, NQ = 2 * NI, NP = 4 * C::MT, kAhead = 3, NB = kAhead + 1;
+      bf16x8 kf[NB];
+      u32x4 vf[NB];
+      auto k_fetch = [&](int j) __device__ {
+        kf[j % NB] = __builtin_bit_cast(bf16x8, *lds_at<lds_u32x4>(ka[j % NI] + (j / NI) * 32 * RB));
+      };
+      auto v_fetch = [&](int j) __device__ {
+        const int ks4 = j / C::MT, mt = j % C::MT;
+        const bf16v4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(lds_at<lds_bf16v4>(va[mt] + 16 * ks4 * RB));
+        const bf16v4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(lds_at<lds_bf16v4>(va[mt] + (16 * ks4 + 4) * RB));
+        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+        vf[j % NB] = u32x4{l2.x, l2.y, h2.x, h2.y};
+      };
+      float x[2][2], e[2][2], psum = 0.0f;
+      auto args = [&](int p) __device__ {   // pair p: logits 2 p, 2 p + 1 of the lane
+#pragma unroll
+        for (int l = 0; l < 2; ++l) x[p & 1][l] = fmaf(zo[p / 8][2 * (p % 8) + l], c2, -m_run);
+      };
+      auto exps = [&](int p) __device__ {
+#pragma unroll
+        for (int l = 0; l < 2; ++l) e[p & 1][l] = __builtin_amdgcn_exp2f(x[p & 1][l]);
+      };
+      auto sums = [&](int p) __device__ {
+        psum += e[p & 1][0];
+        psum += e[p & 1][1];
+        pp[p / 8][(p / 4) & 1][p & 3] = pack_bf16x2(e[p & 1][0], e[p & 1][1]);
+      };
+      auto pair = [&](int p) __device__ {
+        exps(p);
+        if (p > 0) sums(p - 1);
+        if (p + 1 < 16) args(p + 1);
+      };
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) k_fetch(j);
+      args(0);
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) {
+        __builtin_amdgcn_sched_barrier(0);
+        zn[j / NI] = mfma_step<BF16, D>(kf[j % NB], qf[j % NI], j % NI == 0 ? f32x16{} : zn[j / NI]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + kAhead < NQ)
+          k_fetch(j + kAhead);
+        else
+          v_fetch(j + kAhead - NQ);
+#pragma unroll
+        for (int p = 0; p < 12; ++p)
+          if (p * NQ / 12 == j) pair(p);
+      }
+      float tmax = kNegInf;
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        __builtin_amdgcn_sched_barrier(0);
+        oacc[j % C::MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8, vf[j % NB]),
+            __builtin_bit_cast(bf16x8, pp[j / (2 * C::MT)][(j / C::MT) & 1]), oacc[j % C::MT], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + kAhead < NP) v_fetch(j + kAhead);
+#pragma unroll
+        for (int p = 12; p < 16; ++p)
+          if ((p - 12) * NP / 8 == j) pair(p);
+        if (NP / 2 == j) sums(15);
+#pragma unroll
+        for (int r = 0; r < 32 / NP; ++r)
+          tmax = fmaxf(tmax, zn[j / (NP / 2)][(j % (NP / 2)) * (32 / NP) + r]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      l_run += psum;
+      raise_max(xhalf_max(tmax));
+    }
+  };
+
+  // prologue: K(0) lands in LDS
   dma_k(0, tile_info(a, s, 0), 0);
-  dma_v(0, tile_info(a, s, 0));
   stamp(BM_TL_COPIES_ISSUED);
   tile_fence();
   append_store();
   __syncthreads();
   stamp(BM_TL_FIRST_TILE);
-  f32x16 sl[2];
-  // tile t: K(t) and V(t) are in LDS; K(t+1) and V(t+1) are fetched meanwhile
+  // Step t: K(t) and V(t-1) are in LDS; K(t+1) and V(t) are fetched meanwhile
+  // (last step: sweep 2's first K tile; its position ring slot is free, nobody
+  // reads tile nt - 3's any more).
+  auto fetch1 = [&](int t) __device__ {
+    const uint64_t issue0 = tl_now();
+    const int par = t & 1;
+    if (t + 1 < nt)
+      dma_k(par ^ 1, tile_info(a, s, t + 1), t + 1);
+    else if (a.accumulate)
+      dma_k(par ^ 1, tile_info2(a, s, 0), nt);
+    dma_v(par, tile_info(a, s, t));
+    if constexpr (kTimeline) tl[BM_TL_S1_COPY_ISSUE] += tl_now() - issue0;
+  };
+  bool p_live = false;   // P of the tile before waits for its PV product
+  // one step with running maxima: PV of tile t - 1, then tile t's logits and P
   auto sweep1_step = [&](auto mask_tag, int t) __device__ {
     const int par = t & 1;
     const TileInfo ti = tile_info(a, s, t);
-    const uint64_t issue0 = tl_now();
-    if (t + 1 < nt) {
-      const TileInfo tn = tile_info(a, s, t + 1);
-      dma_k(par ^ 1, tn, t + 1);
-      dma_v(par ^ 1, tn);
-    } else if (a.accumulate) {
-      // sweep 2's first K tile (its position ring slot: nobody reads tile
-      // nt - 3's any more)
-      dma_k(par ^ 1, tile_info(a, s, 0), nt);
-    }
-    if constexpr (kTimeline) tl[BM_TL_S1_COPY_ISSUE] += tl_now() - issue0;
-    if (!decltype(mask_tag)::value || tile_active(s, ti)) {
+    fetch1(t);
+    if (p_live) pv_tile(vbuf + (par ^ 1) * C::TILE_BYTES);
+    p_live = !decltype(mask_tag)::value || tile_active(s, ti);
+    if (p_live) {
       qk_st(kbuf + par * C::TILE_BYTES, sl);
       if constexpr (PAD) {
         const uint64_t padk = pad_bits(ti, pk_ring[t % 3]);
         if (padk) hide_pads(sl, padk);
       }
-      sweep1_tile(mask_tag, sl, vbuf + par * C::TILE_BYTES, ti);
+      softmax_tile(mask_tag, ti);
     }
     wait_and_sync(BM_TL_S1_WAIT, BM_TL_S1_BARRIER);
   };
-  // two loops, so that the common one holds no second path (a masked and an
-  // unmasked tile behind a branch made the compiler keep the accumulators twice)
+  // Runs of tiles without a mask and the masked ones after each: the whole cache
+  // tiles and a partial one, then the block's tiles up to the diagonal (one run
+  // in all when no partial tile lies between).
   int t1 = 0;
-  for (; t1 < s.nun; ++t1) sweep1_step(std::false_type{}, t1);
-  for (; t1 < nt; ++t1) sweep1_step(std::true_type{}, t1);
+#pragma nounroll
+  for (int run = 0; t1 < nt; ++run) {
+    const bool split = s.part && run == 0;
+    const int run_end = !s.wave_active ? t1 : split ? s.ncf : s.ncf + s.part + s.nbu;
+    if constexpr (FAST) {
+      if (t1 < run_end) {
+        fetch1(t1);
+        if (p_live) pv_tile(vbuf + ((t1 & 1) ^ 1) * C::TILE_BYTES);
+        qk_st(kbuf + (t1 & 1) * C::TILE_BYTES, sl);
+        float tmax = kNegInf;
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sl[st][r]);
+        raise_max(xhalf_max(tmax));
+        wait_and_sync(BM_TL_S1_WAIT, BM_TL_S1_BARRIER);
+        // operand addresses: K of parity t & 1, V of the other one (the buffers
+        // of the two parities differ in one address bit)
+        uint32_t ka[C::QSTEPS], va[C::MT];
+#pragma unroll
+        for (int i = 0; i < C::QSTEPS; ++i)
+          ka[i] = lds0 + (t1 & 1) * C::TILE_BYTES + (uint32_t)(frag0 ^ (32 * i));
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt)
+          va[mt] = lds0 + (2 + ((t1 & 1) ^ 1)) * C::TILE_BYTES + (uint32_t)(vbase ^ (64 * mt));
+        auto step = [&](f32x16 (&zn)[2], const f32x16 (&zo)[2], int t) __device__ {
+          fetch1(t);
+#pragma unroll
+          for (int i = 0; i < C::QSTEPS; ++i) ka[i] ^= C::TILE_BYTES;
+#pragma unroll
+          for (int mt = 0; mt < C::MT; ++mt) va[mt] ^= C::TILE_BYTES;
+          interleaved_step(zn, zo, ka, va);
+          wait_and_sync(BM_TL_S1_WAIT, BM_TL_S1_BARRIER);
+        };
+        f32x16 sm[2];   // logits alternate between sl and sm
+        for (++t1; t1 + 1 < run_end; t1 += 2) {
+          step(sm, sl, t1);
+          step(sl, sm, t1 + 1);
+        }
+        if (t1 < run_end) {
+          step(sm, sl, t1);
+          sl[0] = sm[0];
+          sl[1] = sm[1];
+          ++t1;
+        }
+        // the run's last tile: P (its PV product belongs to the next step)
+        exp_tile(m_run);
+        p_live = true;
+      }
+    } else {
+      for (; t1 < run_end; ++t1) sweep1_step(std::false_type{}, t1);
+    }
+    const int masked_end = split ? s.ncf + 1 : nt;
+    for (; t1 < masked_end; ++t1) sweep1_step(std::true_type{}, t1);
+  }
+  if (p_live) pv_tile(vbuf + ((nt - 1) & 1) * C::TILE_BYTES);
+  if constexpr (BF16) __syncthreads();   // the V buffers are free for the output rows
   stamp(BM_TL_SWEEP1_END);
 
   // ---- finish rows: normalise, store O, row log-sum-exp (log2 units) ----
@@ -736,16 +933,35 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   };
 
   stamp(BM_TL_SWEEP2_START);
-  // tile t: K(t) is in LDS (sweep 1's last step fetched K(0)); K(t+1) is
-  // fetched meanwhile
+  // Step t: K(t) is in LDS (sweep 1's last step fetched K(0)); K(t+1) is fetched
+  // meanwhile.  After the step's barrier tile t - 1's sums of all waves are in cs.
+  auto fetch2 = [&](int t) __device__ {
+    if (t + 1 < nt) dma_k((nt + t + 1) & 1, tile_info2(a, s, t + 1), nt + t + 1);
+  };
+  // add the waves' sums of tile t (the waves take turns)
+  auto store_sums = [&](int t) __device__ {
+    const TileInfo ti = tile_info2(a, s, t);
+    if (s.w == (t & (kWaves - 1)) && s.lane < ti.valid) {
+      float acc = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) acc += cs[t % 3][w][s.lane];
+      partial[ti.slot0 + s.lane] = acc;
+      if (wg_last) {
+        float lw = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) lw += lws[t % 3][w][s.lane];
+        a.lastw[(int64_t)s.u * a.cap + ti.slot0 + s.lane] = lw;
+      }
+    }
+  };
   auto sweep2_step = [&](auto mask_tag, int t) __device__ {
-    const int par = (nt + t) & 1;
-    const TileInfo ti = tile_info(a, s, t);
+    const TileInfo ti = tile_info2(a, s, t);
+    float (*ct)[kKeyTile] = cs[t % 3];
     f32x16* cur = sl;
-    if (t + 1 < nt) dma_k(par ^ 1, tile_info(a, s, t + 1), nt + t + 1);
+    fetch2(t);
     if (!decltype(mask_tag)::value || tile_active(s, ti)) {
-      qk_s(kbuf + par * C::TILE_BYTES, cur);
-      sweep2_tile(mask_tag, cur, ti, cs[par]);
+      qk_s(kbuf + ((nt + t) & 1) * C::TILE_BYTES, cur);
+      sweep2_tile(mask_tag, cur, ti, ct);
       if constexpr (PAD) {
         // a pad key is visible to no real row (pad rows add nothing: lse = +inf)
         const uint64_t padk = pad_bits(ti, pk_ring[(nt + t) % 3]);
@@ -753,13 +969,13 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 #pragma unroll
           for (int st = 0; st < 2; ++st) {
             const int key = 32 * st + kappa(s.n);
-            if ((padk >> key) & 1) cs[par][s.w][key] = 0.0f;
+            if ((padk >> key) & 1) ct[s.w][key] = 0.0f;
           }
         }
       }
     } else if (s.lane < 32) {
-      cs[par][s.w][s.lane] = 0.0f;
-      cs[par][s.w][32 + s.lane] = 0.0f;
+      ct[s.w][s.lane] = 0.0f;
+      ct[s.w][32 + s.lane] = 0.0f;
     }
     if (wg_last) {
       // the last row sees every key of the tile (pads aside)
@@ -776,26 +992,79 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
           v = xhalf_sum(v);
           if (PAD && ((padk >> key) & 1)) v = 0.0f;
         }
-        if (s.h == 0) lws[par][s.w][key] = v;
+        if (s.h == 0) lws[t % 3][s.w][key] = v;
       }
     }
     wait_and_sync(BM_TL_S2_WAIT, BM_TL_S2_BARRIER);
-    if (tid < ti.valid) {
-      float acc = 0.0f;
+    if (t > 0) store_sums(t - 1);
+  };
+  // one half tile of the interleaved loop: QK^T of key half U of tile t (into
+  // snew) and the sums of the half before it (sold)
+  auto sums_half = [&](const f32x16& z, int half, int t) __device__ {
+    float csum = 0.0f;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) acc += cs[par][w][tid];
-      partial[ti.slot0 + tid] = acc;
-      if (wg_last) {
-        float lw = 0.0f;
+    for (int r = 0; r < 16; ++r) csum += __builtin_amdgcn_exp2f(fmaf(z[r], c2, -lse_r[r]));
+    csum = xhalf_sum(csum);
+    if (s.h == 0) cs[t % 3][s.w][32 * half + kappa(s.n)] = csum;
+  };
+  // one tile of the interleaved loop: half by half, QK^T of tile t and the sums
+  // of the half before it
+  auto interleaved_tile2 = [&](uint32_t (&ka)[C::QSTEPS], int t) __device__ {
+    if constexpr (FAST) {
+      constexpr int NI = C::QSTEPS, LPI = 16 / NI, kAhead = 3, NB = kAhead + 1;
+      bf16x8 kf[NB];
+      auto fetch = [&](int j) __device__ {
+        kf[j % NB] = __builtin_bit_cast(bf16x8, *lds_at<lds_u32x4>(ka[j % NI] + (j / NI) * 32 * RB));
+      };
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) lw += lws[par][w][tid];
-        a.lastw[(int64_t)s.u * a.cap + ti.slot0 + tid] = lw;
+      for (int j = 0; j < kAhead; ++j) fetch(j);
+      float csum[2] = {0.0f, 0.0f};
+#pragma unroll
+      for (int j = 0; j < 2 * NI; ++j) {
+        const int u = j / NI, i = j % NI;
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + kAhead < 2 * NI) fetch(j + kAhead);
+#pragma unroll
+        for (int l = 0; l < LPI; ++l)
+          csum[u] += __builtin_amdgcn_exp2f(fmaf(sl[u ^ 1][i * LPI + l], c2, -lse_r[i * LPI + l]));
+        __builtin_amdgcn_sched_barrier(0);
+        sl[u] = mfma_step<BF16, D>(qf[i], kf[j % NB], i == 0 ? f32x16{} : sl[u]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      csum[0] = xhalf_sum(csum[0]);
+      csum[1] = xhalf_sum(csum[1]);
+      if (s.h == 0) {
+        cs[(t - 1) % 3][s.w][32 + kappa(s.n)] = csum[0];
+        cs[t % 3][s.w][kappa(s.n)] = csum[1];
       }
     }
   };
+  // tiles without a mask: the whole cache tiles and the block's up to the diagonal
+  const int nun2 = s.wave_active ? s.ncf + s.nbu : 0;
   int t2 = 0;
-  for (; t2 < s.nun; ++t2) sweep2_step(std::false_type{}, t2);
+  if (FAST && !wg_last && nun2 > 0) {
+    fetch2(0);
+    qk_s(kbuf + (nt & 1) * C::TILE_BYTES, sl);
+    sums_half(sl[0], 0, 0);
+    wait_and_sync(BM_TL_S2_WAIT, BM_TL_S2_BARRIER);
+    uint32_t ka[C::QSTEPS];
+#pragma unroll
+    for (int i = 0; i < C::QSTEPS; ++i)
+      ka[i] = lds0 + (nt & 1) * C::TILE_BYTES + (uint32_t)(frag0 ^ (32 * i));
+    for (t2 = 1; t2 < nun2; ++t2) {
+      fetch2(t2);
+#pragma unroll
+      for (int i = 0; i < C::QSTEPS; ++i) ka[i] ^= C::TILE_BYTES;
+      interleaved_tile2(ka, t2);
+      wait_and_sync(BM_TL_S2_WAIT, BM_TL_S2_BARRIER);
+      store_sums(t2 - 1);
+    }
+    sums_half(sl[1], 1, t2 - 1);
+  }
+  for (; t2 < nun2; ++t2) sweep2_step(std::false_type{}, t2);
   for (; t2 < nt; ++t2) sweep2_step(std::true_type{}, t2);
+  __syncthreads();
+  store_sums(nt - 1);
   timeline_end();
 }
 
