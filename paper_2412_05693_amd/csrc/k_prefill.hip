@@ -33,11 +33,16 @@
 
 #include "bm_internal.h"
 
+// a lambda of the kernel, always part of it: as a call (which the compiler would
+// make of the larger float32 ones) it would move the registers it uses to memory
+#define BM_LAMBDA __device__ __attribute__((always_inline))
+
 namespace bm {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -109,6 +114,7 @@ template <bool BF16, int D>
 struct Cfg {
   using E = typename std::conditional<BF16, uint16_t, float>::type;
   using qfrag_t = typename std::conditional<BF16, bf16x8, float>::type;
+  using kfrag_t = typename std::conditional<BF16, bf16x8, f32x4>::type;   // one 16-byte read
   static constexpr int RB = D * (int)sizeof(E);          // bytes per K/V row
   static constexpr int CPR = RB / 16;                     // 16-byte chunks per row
   static constexpr int TILE_BYTES = kKeyTile * RB;        // one K or V tile in LDS
@@ -155,13 +161,11 @@ __device__ __forceinline__ int k_frag0(int n, int h) {
   const int c = BF16 ? h : h * (C::CPR / 2);
   return n * C::RB + (c ^ swz_k<BF16, D>(n)) * 16;
 }
+// fp32: the same address rule for the chunk that holds K-steps 4 kk .. 4 kk + 3
 template <bool BF16, int D>
-__device__ __forceinline__ typename Cfg<BF16, D>::qfrag_t k_frag(const char* ks, int frag0, int kk) {
-  if constexpr (BF16) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + (frag0 ^ (32 * kk))));
-  } else {
-    return *reinterpret_cast<const float*>(ks + (frag0 ^ (16 * (kk >> 2))) + 4 * (kk & 3));
-  }
+__device__ __forceinline__ typename Cfg<BF16, D>::kfrag_t k_frag(const char* ks, int frag0, int kk) {
+  return __builtin_bit_cast(typename Cfg<BF16, D>::kfrag_t,
+                            *reinterpret_cast<const u32x4*>(ks + (frag0 ^ ((BF16 ? 32 : 16) * kk))));
 }
 
 struct Geo {
@@ -322,10 +326,10 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   if constexpr (kTimeline) tl[BM_TL_ENTRY] = tl_now();
   const Geo s = make_geo<G, PAD>(a);
   const int tid = threadIdx.x;
-  auto stamp = [&](int field) __device__ {
+  auto stamp = [&](int field) BM_LAMBDA {
     if constexpr (kTimeline) tl[field] = tl_now();
   };
-  auto timeline_end = [&]() __device__ {
+  auto timeline_end = [&]() BM_LAMBDA {
     if constexpr (kTimeline) {
       tl[BM_TL_END] = tl_now();
       // HW_ID (all 32 bits) and, above it, XCC_ID (hardware registers 4 and 20)
@@ -337,7 +341,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     }
   };
   // end of a tile: wait for this wave's copies, then for every wave
-  auto wait_and_sync = [&](int f_wait, int f_barrier) __device__ {
+  auto wait_and_sync = [&](int f_wait, int f_barrier) BM_LAMBDA {
     if constexpr (kTimeline) {
       const uint64_t a0 = tl_now();
       tile_fence();
@@ -376,7 +380,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
       }
     }
   }
-  auto append_store = [&]() __device__ {
+  auto append_store = [&]() BM_LAMBDA {
     E* kc = static_cast<E*>(a.kc);
     E* vc = static_cast<E*>(a.vc);
 #pragma unroll
@@ -398,12 +402,12 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   const uint64_t vc_base = (uint64_t)(static_cast<const E*>(a.vc) + (int64_t)s.u * a.cap * D);
   const uint64_t ki_base = (uint64_t)(static_cast<const E*>(a.kin) + plane * D);
   const uint64_t vi_base = (uint64_t)(static_cast<const E*>(a.vin) + plane * D);
-  auto rsrc_of = [&](uint64_t p, int bytes) __device__ {
+  auto rsrc_of = [&](uint64_t p, int bytes) BM_LAMBDA {
     return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)p),
                  (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(p >> 32)) & 0xFFFFu,
                  (uint32_t)__builtin_amdgcn_readfirstlane(bytes), (uint32_t)kRsrcWord3};
   };
-  auto tile_src = [&](const TileInfo& ti, bool kside) __device__ {
+  auto tile_src = [&](const TileInfo& ti, bool kside) BM_LAMBDA {
     const uint64_t p = ti.cache ? (kside ? kc_base : vc_base) : (kside ? ki_base : vi_base);
     return rsrc_of(p + (uint64_t)(ti.base * RB) - kBias,
                    ((ti.cache ? a.len0 : s.in_rows) - ti.base) * RB + kBias);
@@ -416,7 +420,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     voff[j] = copy_offset<BF16, D, false>(s, j);
   }
   const uint64_t pos_base = (uint64_t)(a.pos + (int64_t)s.u * a.cap);
-  auto dma_k = [&](int par, const TileInfo& ti, int t) __device__ {
+  auto dma_k = [&](int par, const TileInfo& ti, int t) BM_LAMBDA {
     copy_tile(lds0 + par * C::TILE_BYTES, tile_src(ti, true), koff, s.w);
     if (PAD && s.pad > 0 && ti.cache && s.w == 0) {
       // the tile's key positions, in key order, next to the K rows
@@ -429,13 +433,13 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   };
   // bit k set: key k of tile ti is a pad token (cache keys through the LDS copy
   // of their positions); uniform across the workgroup
-  auto pad_bits = [&](const TileInfo& ti, const int32_t* pk) __device__ -> uint64_t {
+  auto pad_bits = [&](const TileInfo& ti, const int32_t* pk) BM_LAMBDA -> uint64_t {
     if (!PAD || s.pad == 0) return 0;
     if (ti.cache) return __ballot(pk[s.lane] < s.pad);
     const int n = min(max(s.pad - a.t0 - ti.base, 0), kKeyTile);
     return n >= 64 ? ~0ull : ((1ull << n) - 1);
   };
-  auto dma_v = [&](int par, const TileInfo& ti) __device__ {
+  auto dma_v = [&](int par, const TileInfo& ti) BM_LAMBDA {
     copy_tile(lds0 + (2 + par) * C::TILE_BYTES, tile_src(ti, false), voff, s.w);
   };
 
@@ -467,25 +471,32 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // logits of one tile: S^T (one query per lane) or S (one key per lane); the
   // K fragments of step kk + 1 are read while the MFMAs of step kk run
   const int frag0 = k_frag0<BF16, D>(s.n, s.h);
-  auto qk_tile = [&](auto st_tag, const char* ks, f32x16* acc) __device__ {
+  auto qk_tile = [&](auto st_tag, const char* ks, f32x16* acc) BM_LAMBDA {
     constexpr bool ST = decltype(st_tag)::value;
     int f0 = frag0;
     asm volatile("" : "+v"(f0));   // the swizzled addresses are formed here, not kept
     acc[0] = f32x16{};
     acc[1] = f32x16{};
-    typename C::qfrag_t kf[2][2];
+    constexpr int SPR = BF16 ? 1 : 4;   // K-steps per read
+    typename C::kfrag_t kf[2][2];
     kf[0][0] = k_frag<BF16, D>(ks, f0, 0);
     kf[0][1] = k_frag<BF16, D>(ks + 32 * RB, f0, 0);
 #pragma unroll
-    for (int kk = 0; kk < C::QSTEPS; ++kk) {
-      if (kk + 1 < C::QSTEPS) {
-        kf[(kk + 1) & 1][0] = k_frag<BF16, D>(ks, f0, kk + 1);
-        kf[(kk + 1) & 1][1] = k_frag<BF16, D>(ks + 32 * RB, f0, kk + 1);
+    for (int kr = 0; kr < C::QSTEPS / SPR; ++kr) {
+      if (kr + 1 < C::QSTEPS / SPR) {
+        kf[(kr + 1) & 1][0] = k_frag<BF16, D>(ks, f0, kr + 1);
+        kf[(kr + 1) & 1][1] = k_frag<BF16, D>(ks + 32 * RB, f0, kr + 1);
       }
 #pragma unroll
-      for (int st = 0; st < 2; ++st)
-        acc[st] = ST ? mfma_step<BF16, D>(kf[kk & 1][st], qf[kk], acc[st])
-                     : mfma_step<BF16, D>(qf[kk], kf[kk & 1][st], acc[st]);
+      for (int e = 0; e < SPR; ++e)
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+          typename C::qfrag_t kv;
+          if constexpr (BF16) kv = kf[kr & 1][st];
+          else kv = kf[kr & 1][st][e];
+          acc[st] = ST ? mfma_step<BF16, D>(kv, qf[kr * SPR + e], acc[st])
+                       : mfma_step<BF16, D>(qf[kr * SPR + e], kv, acc[st]);
+        }
     }
     if constexpr (BF16) {
       // pin the order: the reads of step kk + 1 go out before the MFMAs of
@@ -499,8 +510,8 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
       __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
     }
   };
-  auto qk_st = [&](const char* ks, f32x16* acc) __device__ { qk_tile(std::true_type{}, ks, acc); };
-  auto qk_s = [&](const char* ks, f32x16* acc) __device__ { qk_tile(std::false_type{}, ks, acc); };
+  auto qk_st = [&](const char* ks, f32x16* acc) BM_LAMBDA { qk_tile(std::true_type{}, ks, acc); };
+  auto qk_s = [&](const char* ks, f32x16* acc) BM_LAMBDA { qk_tile(std::false_type{}, ks, acc); };
 
   // ======================= sweep 1: online softmax + PV =======================
   f32x16 oacc[C::MT];
@@ -511,7 +522,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // left padding: a real query row sees no pad key (a pad row keeps its causal
   // keys; its output and score contributions are dropped later).  The lane's
   // keys all have bit 3 equal to h, so the pad bits are shifted once.
-  auto hide_pads = [&](f32x16* sacc, uint64_t padk) __device__ {
+  auto hide_pads = [&](f32x16* sacc, uint64_t padk) BM_LAMBDA {
     const uint64_t hide = s.qpad ? 0 : (padk >> (8 * s.h));
 #pragma unroll
     for (int st = 0; st < 2; ++st)
@@ -524,7 +535,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // MFMA's B operand; fp32: P replaces the logits in sl
   f32x16 sl[2];
   u32x4 pp[2][2];
-  auto pack_p = [&](int half) __device__ {
+  auto pack_p = [&](int half) BM_LAMBDA {
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -534,7 +545,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // The reference m_run moves only when some row of the wave sees a logit more
   // than kRescaleLog2 above it: the probabilities stay below 2^kRescaleLog2
   // (exact in fp32, fine in bf16) and the O rescale is rare.
-  auto raise_max = [&](float tmax) __device__ {
+  auto raise_max = [&](float tmax) BM_LAMBDA {
     if (__ballot(tmax * c2 > m_run + kRescaleLog2) != 0) {
       const float m_new = fmaxf(m_run, tmax * c2);
       // (a padded row that has seen no key yet keeps m = -inf: nothing to scale)
@@ -547,7 +558,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
         for (int r = 0; r < 16; ++r) oacc[mt][r] *= alpha;
     }
   };
-  auto exp_tile = [&](float m_sub) __device__ {
+  auto exp_tile = [&](float m_sub) BM_LAMBDA {
     float psum = 0.0f;
 #pragma unroll
     for (int st = 0; st < 2; ++st)
@@ -563,7 +574,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
       pack_p(1);
     }
   };
-  auto softmax_tile = [&](auto mask_tag, const TileInfo& ti) __device__ {
+  auto softmax_tile = [&](auto mask_tag, const TileInfo& ti) BM_LAMBDA {
     constexpr bool MASK = decltype(mask_tag)::value;
     f32x16* sacc = sl;
     if constexpr (MASK) {
@@ -599,15 +610,16 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   const int j16 = s.lane & 15, dhalf = (s.lane >> 4) & 1;
   const int vrow = 8 * s.h + (j16 >> 2);
   const int vbase = vrow * RB + 16 * swz_v<BF16, D>(vrow) + (16 * dhalf + 4 * (j16 & 3)) * 2;
-  auto v_frag = [&](const char* vs, int vb, int ks4, int mt) __device__ {
+  auto v_frag = [&](const char* vs, int vb, int ks4, int mt) BM_LAMBDA {
     const char* p = vs + (vb ^ (64 * mt)) + 16 * ks4 * RB;
     const bf16v4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)p);
     const bf16v4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16v4*)(p + 4 * RB));
     const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
     return u32x4{l2.x, l2.y, h2.x, h2.y};
   };
+  typedef __attribute__((ext_vector_type(C::MT))) float vrow_t;
   // O^T += V^T P^T of one tile
-  auto pv_tile = [&](const char* vs) __device__ {
+  auto pv_tile = [&](const char* vs) BM_LAMBDA {
     if constexpr (BF16) {
       int vb = vbase;
       asm volatile("" : "+v"(vb));
@@ -631,12 +643,13 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
       for (int st = 0; st < 2; ++st)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
+          // M-tile mt, row n stands for d = MT n + mt, so that a lane's values of
+          // all M-tiles are neighbours: one read per key
           const int key = st_key(st, r >> 2, r & 3, s.h);
+          const vrow_t vv = *reinterpret_cast<const vrow_t*>(vs + key * RB + s.n * (4 * C::MT));
 #pragma unroll
-          for (int mt = 0; mt < C::MT; ++mt) {
-            const float vv = *reinterpret_cast<const float*>(vs + key * RB + (32 * mt + s.n) * 4);
-            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, sl[st][r], oacc[mt], 0, 0, 0);
-          }
+          for (int mt = 0; mt < C::MT; ++mt)
+            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[mt], sl[st][r], oacc[mt], 0, 0, 0);
         }
     }
   };
@@ -656,15 +669,15 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // LDS base: full cache b=4 s=8192 2702 -> 2582 us, b=1 s=4096 556 -> 528 us,
   // b=256 s=2048 (power-bound) 2% faster.
   auto interleaved_step = [&](f32x16 (&zn)[2], const f32x16 (&zo)[2], uint32_t (&ka)[C::QSTEPS],
-                              uint32_t (&va)[C::MT]) __device__ {
+                              uint32_t (&va)[C::MT]) BM_LAMBDA {
     if constexpr (FAST) {
       constexpr int NI = C::QSTEPS, NQ = 2 * NI, NP = 4 * C::MT, kAhead = 3, NB = kAhead + 1;
       bf16x8 kf[NB];
       u32x4 vf[NB];
-      auto k_fetch = [&](int j) __device__ {
+      auto k_fetch = [&](int j) BM_LAMBDA {
         kf[j % NB] = __builtin_bit_cast(bf16x8, *lds_at<lds_u32x4>(ka[j % NI] + (j / NI) * 32 * RB));
       };
-      auto v_fetch = [&](int j) __device__ {
+      auto v_fetch = [&](int j) BM_LAMBDA {
         const int ks4 = j / C::MT, mt = j % C::MT;
         const bf16v4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(lds_at<lds_bf16v4>(va[mt] + 16 * ks4 * RB));
         const bf16v4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(lds_at<lds_bf16v4>(va[mt] + (16 * ks4 + 4) * RB));
@@ -672,20 +685,20 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
         vf[j % NB] = u32x4{l2.x, l2.y, h2.x, h2.y};
       };
       float x[2][2], e[2][2], psum = 0.0f;
-      auto args = [&](int p) __device__ {   // pair p: logits 2 p, 2 p + 1 of the lane
+      auto args = [&](int p) BM_LAMBDA {   // pair p: logits 2 p, 2 p + 1 of the lane
 #pragma unroll
         for (int l = 0; l < 2; ++l) x[p & 1][l] = fmaf(zo[p / 8][2 * (p % 8) + l], c2, -m_run);
       };
-      auto exps = [&](int p) __device__ {
+      auto exps = [&](int p) BM_LAMBDA {
 #pragma unroll
         for (int l = 0; l < 2; ++l) e[p & 1][l] = __builtin_amdgcn_exp2f(x[p & 1][l]);
       };
-      auto sums = [&](int p) __device__ {
+      auto sums = [&](int p) BM_LAMBDA {
         psum += e[p & 1][0];
         psum += e[p & 1][1];
         pp[p / 8][(p / 4) & 1][p & 3] = pack_bf16x2(e[p & 1][0], e[p & 1][1]);
       };
-      auto pair = [&](int p) __device__ {
+      auto pair = [&](int p) BM_LAMBDA {
         exps(p);
         if (p > 0) sums(p - 1);
         if (p + 1 < 16) args(p + 1);
@@ -739,7 +752,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // Step t: K(t) and V(t-1) are in LDS; K(t+1) and V(t) are fetched meanwhile
   // (last step: sweep 2's first K tile; its position ring slot is free, nobody
   // reads tile nt - 3's any more).
-  auto fetch1 = [&](int t) __device__ {
+  auto fetch1 = [&](int t) BM_LAMBDA {
     const uint64_t issue0 = tl_now();
     const int par = t & 1;
     if (t + 1 < nt)
@@ -751,7 +764,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   };
   bool p_live = false;   // P of the tile before waits for its PV product
   // one step with running maxima: PV of tile t - 1, then tile t's logits and P
-  auto sweep1_step = [&](auto mask_tag, int t) __device__ {
+  auto sweep1_step = [&](auto mask_tag, int t) BM_LAMBDA {
     const int par = t & 1;
     const TileInfo ti = tile_info(a, s, t);
     fetch1(t);
@@ -796,7 +809,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt)
           va[mt] = lds0 + (2 + ((t1 & 1) ^ 1)) * C::TILE_BYTES + (uint32_t)(vbase ^ (64 * mt));
-        auto step = [&](f32x16 (&zn)[2], const f32x16 (&zo)[2], int t) __device__ {
+        auto step = [&](f32x16 (&zn)[2], const f32x16 (&zo)[2], int t) BM_LAMBDA {
           fetch1(t);
 #pragma unroll
           for (int i = 0; i < C::QSTEPS; ++i) ka[i] ^= C::TILE_BYTES;
@@ -875,14 +888,13 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
       asm volatile("" : "+v"(orow), "+v"(ohead));
       E* o = static_cast<E*>(a.o) + ((int64_t)ohead * a.seq_ld + orow) * D;
 #pragma unroll
-      for (int mt = 0; mt < C::MT; ++mt)
+      for (int r = 0; r < 16; ++r) {
+        const int row = 8 * (r >> 2) + 4 * s.h + (r & 3);
+        vrow_t x;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int d0 = 32 * mt + 8 * i + 4 * s.h;
-          const float x0 = oacc[mt][4 * i + 0] * sc, x1 = oacc[mt][4 * i + 1] * sc;
-          const float x2 = oacc[mt][4 * i + 2] * sc, x3 = oacc[mt][4 * i + 3] * sc;
-          *reinterpret_cast<float4*>(o + d0) = make_float4(x0, x1, x2, x3);
-        }
+        for (int mt = 0; mt < C::MT; ++mt) x[mt] = oacc[mt][r] * sc;
+        *reinterpret_cast<vrow_t*>(o + C::MT * row) = x;
+      }
     }
   }
 
@@ -911,7 +923,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 #pragma unroll
   for (int r = 1; r < 16; ++r) lse_last = r == ri ? lse_r[r] : lse_last;
 
-  auto sweep2_tile = [&](auto mask_tag, f32x16* acc, const TileInfo& ti, float (*cs)[kKeyTile]) __device__ {
+  auto sweep2_tile = [&](auto mask_tag, f32x16* acc, const TileInfo& ti, float (*cs)[kKeyTile]) BM_LAMBDA {
     constexpr bool MASK = decltype(mask_tag)::value;
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -935,11 +947,11 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   stamp(BM_TL_SWEEP2_START);
   // Step t: K(t) is in LDS (sweep 1's last step fetched K(0)); K(t+1) is fetched
   // meanwhile.  After the step's barrier tile t - 1's sums of all waves are in cs.
-  auto fetch2 = [&](int t) __device__ {
+  auto fetch2 = [&](int t) BM_LAMBDA {
     if (t + 1 < nt) dma_k((nt + t + 1) & 1, tile_info2(a, s, t + 1), nt + t + 1);
   };
   // add the waves' sums of tile t (the waves take turns)
-  auto store_sums = [&](int t) __device__ {
+  auto store_sums = [&](int t) BM_LAMBDA {
     const TileInfo ti = tile_info2(a, s, t);
     if (s.w == (t & (kWaves - 1)) && s.lane < ti.valid) {
       float acc = 0.0f;
@@ -954,7 +966,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
       }
     }
   };
-  auto sweep2_step = [&](auto mask_tag, int t) __device__ {
+  auto sweep2_step = [&](auto mask_tag, int t) BM_LAMBDA {
     const TileInfo ti = tile_info2(a, s, t);
     float (*ct)[kKeyTile] = cs[t % 3];
     f32x16* cur = sl;
@@ -1000,7 +1012,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   };
   // one half tile of the interleaved loop: QK^T of key half U of tile t (into
   // snew) and the sums of the half before it (sold)
-  auto sums_half = [&](const f32x16& z, int half, int t) __device__ {
+  auto sums_half = [&](const f32x16& z, int half, int t) BM_LAMBDA {
     float csum = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) csum += __builtin_amdgcn_exp2f(fmaf(z[r], c2, -lse_r[r]));
@@ -1009,11 +1021,11 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   };
   // one tile of the interleaved loop: half by half, QK^T of tile t and the sums
   // of the half before it
-  auto interleaved_tile2 = [&](uint32_t (&ka)[C::QSTEPS], int t) __device__ {
+  auto interleaved_tile2 = [&](uint32_t (&ka)[C::QSTEPS], int t) BM_LAMBDA {
     if constexpr (FAST) {
       constexpr int NI = C::QSTEPS, LPI = 16 / NI, kAhead = 3, NB = kAhead + 1;
       bf16x8 kf[NB];
-      auto fetch = [&](int j) __device__ {
+      auto fetch = [&](int j) BM_LAMBDA {
         kf[j % NB] = __builtin_bit_cast(bf16x8, *lds_at<lds_u32x4>(ka[j % NI] + (j / NI) * 32 * RB));
       };
 #pragma unroll
