@@ -24,6 +24,8 @@ constexpr int kMaxCap = 4096;          // cuts keep up to this many keys in regi
 constexpr int kMaxCapAny = 1 << 16;    // slots per unit (larger cuts stream their keys)
 constexpr int kMaxDecodeLen = 4097;    // entries one decode step attends to (LDS rows)
 constexpr int kMaxBlock = 1024;
+// MI355X's last-level (Infinity) cache: 256 MiB
+constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;
 
 // Ranking key of a cut packed with the position into 64 bits, (key bits << 32
 // | pos); every key is >= 0 (scores are sums of probabilities), so the integer

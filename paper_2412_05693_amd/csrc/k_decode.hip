@@ -410,9 +410,6 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   if (tid == 0) a.len[u] = evict ? len0 : len0 + 1;
 }
 
-// MI355X's last-level (Infinity) cache: 256 MiB
-constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;
-
 template <bool BF16, int D, int G>
 hipError_t launch_t(const DecodeArgs& a, hipStream_t stream) {
   const int L = a.len0 + 1;

@@ -6,7 +6,7 @@
 // kChunk keys (flash-decoding): decode_split_kernel, grid (units, chunks), gives
 // each chunk's partial softmax -- its log2-domain maximum m, its sum l of
 // exp2(z - m) and the unnormalised output o = sum exp2(z - m) v -- for all G
-// query heads of the unit; decode_combine_kernel, one workgroup per unit, merges
+// query heads of the unit; decode_combine_kernel, one workgroup per unit and head, merges
 // the chunks, o = sum_c 2^(m_c - M) o_c / sum_c 2^(m_c - M) l_c with M the
 // largest m_c, writes the outputs and appends the step's pair to the cache
 // (score 0, pos = the step's position).
@@ -25,7 +25,9 @@ namespace bm {
 namespace {
 
 constexpr int kChunk = 512;   // keys per split workgroup
+constexpr int kMaxSplits = kMaxCapAny / kChunk;
 constexpr float kNegInf = -__builtin_huge_valf();
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 // one 16-byte chunk of a row as floats (8 bf16 or 4 float32 elements)
 template <bool BF16>
@@ -43,7 +45,16 @@ __device__ __forceinline__ void unpack_chunk(const uint4 w, float* x) {
   }
 }
 
-template <bool BF16, int D, int G>
+template <bool NT>
+__device__ __forceinline__ uint4 load_row(const void* p) {
+  if constexpr (NT) {
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+  } else {
+    return *reinterpret_cast<const uint4*>(p);
+  }
+}
+
+template <bool BF16, int D, int G, bool NT>
 __global__ void __launch_bounds__(256) decode_split_kernel(LongDecodeArgs a) {
   using E = typename std::conditional<BF16, uint16_t, float>::type;
   constexpr int EPC = 16 / sizeof(E);     // elements per 16-byte chunk
@@ -90,7 +101,7 @@ __global__ void __launch_bounds__(256) decode_split_kernel(LongDecodeArgs a) {
     uint4 raw[UL];
 #pragma unroll
     for (int i = 0; i < UL; ++i)
-      raw[i] = *reinterpret_cast<const uint4*>(k_src(base + 4 * RPL * i + r_in) + ch * EPC);
+      raw[i] = load_row<NT>(k_src(base + 4 * RPL * i + r_in) + ch * EPC);
 #pragma unroll
     for (int i = 0; i < UL; ++i) {
       const int r = base + 4 * RPL * i + r_in;
@@ -156,7 +167,7 @@ __global__ void __launch_bounds__(256) decode_split_kernel(LongDecodeArgs a) {
     uint4 raw[UL];
 #pragma unroll
     for (int i = 0; i < UL; ++i)
-      raw[i] = *reinterpret_cast<const uint4*>(v_src(base + 4 * RPL * i + r_in) + ch * EPC);
+      raw[i] = load_row<NT>(v_src(base + 4 * RPL * i + r_in) + ch * EPC);
 #pragma unroll
     for (int i = 0; i < UL; ++i) {
       // rows past the chunk's end weigh 0 (their V row is the step's own,
@@ -203,25 +214,51 @@ __global__ void __launch_bounds__(256) decode_split_kernel(LongDecodeArgs a) {
   }
 }
 
+// One workgroup per (unit, query head): 256 / D groups of D threads take every
+// 256 / D-th chunk, so a head's partials are read with many loads in flight (one
+// workgroup per unit, each thread walking all chunks twice, took 19 us for 64
+// units of 17 chunks against 48 us for the split itself).
 template <bool BF16, int D, int G>
 __global__ void __launch_bounds__(256) decode_combine_kernel(LongDecodeArgs a) {
   using E = typename std::conditional<BF16, uint16_t, float>::type;
-  const int u = blockIdx.x;
+  constexpr int NG = 256 / D;               // groups of D threads
+  __shared__ float wgt[kMaxSplits];         // 2^(m_c - M)
+  __shared__ float red[NG][D];
+  __shared__ float s_max[4], s_den[4];
+  const int u = blockIdx.x, g = blockIdx.y;
   const int bi = u / a.n_kv_heads, hk = u - bi * a.n_kv_heads;
-  const int tid = threadIdx.x;
-  const float* part = a.part + (int64_t)u * a.nsplit * G * (D + 2);
-  for (int i = tid; i < G * D; i += 256) {
-    const int g = i / D, e = i - g * D;
-    float M = kNegInf;
-    for (int c = 0; c < a.nsplit; ++c) M = fmaxf(M, part[(c * G + g) * (D + 2) + D]);
-    float num = 0.0f, den = 0.0f;
-    for (int c = 0; c < a.nsplit; ++c) {
-      const float* pc = part + (c * G + g) * (D + 2);
-      const float f = pc[D] == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(pc[D] - M);
-      num = fmaf(f, pc[e], num);
-      den = fmaf(f, pc[D + 1], den);
-    }
-    const float x = num / den;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const float* part = a.part + ((int64_t)u * a.nsplit * G + g) * (D + 2);
+  const int64_t stride = (int64_t)G * (D + 2);   // floats between a head's chunks
+  const int n = a.nsplit;
+  // chunk weights; thread c holds chunk c (and c + 256, ... of very long caches)
+  float m = kNegInf;
+  for (int c = tid; c < n; c += 256) m = fmaxf(m, part[c * stride + D]);
+  m = lanes::wave_max(m);
+  if (lane == 0) s_max[w] = m;
+  __syncthreads();
+  const float M = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+  float den = 0.0f;
+  for (int c = tid; c < n; c += 256) {
+    const float mc = part[c * stride + D];
+    const float f = mc == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(mc - M);
+    wgt[c] = f;
+    den = fmaf(f, part[c * stride + D + 1], den);
+  }
+  den = lanes::wave_sum(den);
+  if (lane == 0) s_den[w] = den;
+  __syncthreads();
+  const int gi = tid / D, e = tid - gi * D;
+  float num = 0.0f;
+#pragma unroll 4
+  for (int c = gi; c < n; c += NG) num = fmaf(wgt[c], part[c * stride + e], num);
+  red[gi][e] = num;
+  __syncthreads();
+  if (tid < D) {
+    float x = red[0][e];
+#pragma unroll
+    for (int i = 1; i < NG; ++i) x += red[i][e];
+    x /= s_den[0] + s_den[1] + s_den[2] + s_den[3];
     E* o = static_cast<E*>(a.o) + (((int64_t)bi * a.n_heads + hk * G + g) * a.seq_ld) * D + e;
     if constexpr (BF16) {
       *reinterpret_cast<__bf16*>(o) = (__bf16)x;
@@ -229,6 +266,7 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(LongDecodeArgs a) {
       *o = x;
     }
   }
+  if (g != 0) return;
   // append the step's pair at slot len0
   const int64_t plane = ((int64_t)bi * a.n_kv_heads + hk) * a.seq_ld;
   const E* knew = static_cast<const E*>(a.kin) + plane * D;
@@ -248,12 +286,18 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(LongDecodeArgs a) {
 
 template <bool BF16, int D, int G>
 hipError_t launch_t(const LongDecodeArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL((decode_split_kernel<BF16, D, G>), dim3((unsigned)a.units, (unsigned)a.nsplit),
-                     dim3(256), 0, stream, a);
+  const dim3 grid((unsigned)a.units, (unsigned)a.nsplit);
+  // rows are read once per step: a cache larger than the last-level cache streams
+  // past it, a smaller one stays there for the next step
+  const size_t kv_bytes = (size_t)a.units * 2 * a.len0 * D * (BF16 ? 2 : 4);
+  if (kv_bytes > kLastLevelCacheBytes)
+    hipLaunchKernelGGL((decode_split_kernel<BF16, D, G, true>), grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_split_kernel<BF16, D, G, false>), grid, dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_combine_kernel<BF16, D, G>), dim3((unsigned)a.units), dim3(256), 0,
-                     stream, a);
+  hipLaunchKernelGGL((decode_combine_kernel<BF16, D, G>), dim3((unsigned)a.units, (unsigned)G),
+                     dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
