@@ -3,7 +3,7 @@
 //
 // Decode is bandwidth-bound (the paper notes it reloads the whole cache every
 // step, Sec. 1): the kernel reads each cached K and V row exactly once.  One
-// workgroup per unit (sample, KV head); L = len + 1 entries (len cached slots
+// workgroup of four or eight waves per unit (sample, KV head); L = len + 1 entries (len cached slots
 // plus the step's pair, which sits in a virtual slot `len`).
 //   1. logits z[g][j] = sm_scale * q_g . k_j for the G query heads, kept in LDS
 //      (bf16: a 16x16x32 MFMA per 16 keys, K rows as the A operand straight
@@ -59,14 +59,16 @@ __device__ __forceinline__ u32x4 load_v(const void* p) {
   }
 }
 
-template <bool BF16, int D, int G, bool NTV>
-__global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
+// NW: waves per workgroup
+template <bool BF16, int D, int G, bool NTV, int NW>
+__global__ void __launch_bounds__(64 * NW) decode_kernel(DecodeArgs a) {
+  constexpr int NT = 64 * NW;               // threads
   using E = typename std::conditional<BF16, uint16_t, float>::type;
   constexpr int EPC = 16 / sizeof(E);       // elements per 16-byte chunk
   constexpr int CPR = D / EPC;              // 16-byte chunks per row
   extern __shared__ float dsm[];
-  __shared__ uint64_t s_wkey[4];
-  __shared__ int s_wslot[4];
+  __shared__ uint64_t s_wkey[NW];
+  __shared__ int s_wslot[NW];
   __shared__ float s_inv[4];      // 1 / softmax sum per query head
 
   const int u = blockIdx.x;
@@ -77,8 +79,8 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   const int Lp = (L + 3) & ~3;
   float* P = dsm;                 // [G][Lp] logits, then exp2(logit - max)
   float* sc = P + G * Lp;         // [Lp] scores (prefetched, then updated)
-  float* red = sc + Lp;           // [4][G][D] partial outputs per wave
-  int32_t* pos_s = reinterpret_cast<int32_t*>(red + 4 * G * D);   // [Lp] positions
+  float* red = sc + Lp;           // [NW][G][D] partial outputs per wave
+  int32_t* pos_s = reinterpret_cast<int32_t*>(red + NW * G * D);   // [Lp] positions
 
   const E* kc = static_cast<const E*>(a.kc) + (int64_t)u * a.cap * D;
   const E* vc = static_cast<const E*>(a.vc) + (int64_t)u * a.cap * D;
@@ -90,16 +92,16 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
 
   // Scores and positions (used from the softmax on): the first NSP per thread
   // are loaded into registers here and written to LDS after the logits, so
-  // their latency hides behind the K loads; entries beyond 256 * NSP are
+  // their latency hides behind the K loads; entries beyond NT * NSP are
   // copied after the logits.
-  constexpr int NSP = 4;
+  constexpr int NSP = 1024 / NT;
   const float* score_g = a.score + (int64_t)u * a.cap;
   const int32_t* pos_g = a.pos + (int64_t)u * a.cap;
   float sp_score[NSP];
   int32_t sp_pos[NSP];
 #pragma unroll
   for (int r = 0; r < NSP; ++r) {
-    const int j = min(tid + 256 * r, max(len0 - 1, 0));   // slot 0 exists even when empty
+    const int j = min(tid + NT * r, max(len0 - 1, 0));   // slot 0 exists even when empty
     sp_score[r] = score_g[j];
     sp_pos[r] = pos_g[j];
   }
@@ -146,53 +148,63 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
     constexpr int KD = 2;
     u32x4 kr[KD][D / 32];
 #pragma unroll
-    for (int i = 0; i + 1 < KD; ++i) k_rows(w + 4 * i, kr[i]);
-    for (int kg = w; kg < ngroups; kg += 4 * KD) {
+    for (int i = 0; i + 1 < KD; ++i) k_rows(w + NW * i, kr[i]);
+    for (int kg = w; kg < ngroups; kg += NW * KD) {
 #pragma unroll
       for (int i = 0; i < KD; ++i) {
-        k_rows(kg + 4 * (i + KD - 1), kr[(i + KD - 1) % KD]);
-        if (i == 0 || kg + 4 * i < ngroups) logits(kg + 4 * i, kr[i]);
+        k_rows(kg + NW * (i + KD - 1), kr[(i + KD - 1) % KD]);
+        if (i == 0 || kg + NW * i < ngroups) logits(kg + NW * i, kr[i]);
       }
     }
   } else {
     constexpr int CH = D / 4;               // float4 chunks per row
-    constexpr int NKL = 256 / CH;           // keys in flight per workgroup pass
+    constexpr int NKL = NT / CH;            // keys in flight per workgroup pass
     const int c = tid % CH, kl = tid / CH;
     float4 qr[G];
 #pragma unroll
     for (int g = 0; g < G; ++g)
       qr[g] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(qbase) +
                                                (int64_t)g * a.seq_ld * D + 4 * c);
-    const int iters = (L + NKL - 1) / NKL;
-    for (int it = 0; it < iters; ++it) {
-      const int j = kl + it * NKL;
-      const float* src = j < len0 ? reinterpret_cast<const float*>(kc) + (int64_t)j * D
-                                  : (j == len0 ? reinterpret_cast<const float*>(knew) : nullptr);
-      const float4 kv = src ? *reinterpret_cast<const float4*>(src + 4 * c) : make_float4(0, 0, 0, 0);
+    // eight row loads in flight per lane and none behind a branch (rows past the
+    // last entry read the step's own; their logits are not stored): one load at a
+    // time took 41 us for 600 entries, 40 units
+    constexpr int UK = 8;
+    for (int j0 = kl; j0 < L; j0 += NKL * UK) {
+      float4 kv[UK];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float part = qr[g].x * kv.x + qr[g].y * kv.y + qr[g].z * kv.z + qr[g].w * kv.w;
-        part = lanes::group_sum<CH>(part);
-        if (c == 0 && j < L) P[g * Lp + j] = part * c2;
+      for (int i = 0; i < UK; ++i) {
+        const int j = j0 + i * NKL;
+        const E* src = j < len0 ? kc + (int64_t)j * D : knew;
+        kv[i] = *reinterpret_cast<const float4*>(src + 4 * c);
+      }
+#pragma unroll
+      for (int i = 0; i < UK; ++i) {
+        const int j = j0 + i * NKL;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          float part = qr[g].x * kv[i].x + qr[g].y * kv[i].y + qr[g].z * kv[i].z + qr[g].w * kv[i].w;
+          part = lanes::group_sum<CH>(part);
+          if (c == 0 && j < L) P[g * Lp + j] = part * c2;
+        }
       }
     }
   }
 #pragma unroll
   for (int r = 0; r < NSP; ++r) {
-    const int j = tid + 256 * r;
+    const int j = tid + NT * r;
     if (j < L) {
       sc[j] = j < len0 ? sp_score[r] : 0.0f;
       pos_s[j] = j < len0 ? sp_pos[r] : a.cur_pos;
     }
   }
-  for (int j = tid + 256 * NSP; j < L; j += 256) {
+  for (int j = tid + NT * NSP; j < L; j += NT) {
     sc[j] = j < len0 ? score_g[j] : 0.0f;
     pos_s[j] = j < len0 ? pos_g[j] : a.cur_pos;
   }
   __syncthreads();
 
   // first batch of V rows for phase 4, in flight during the softmax
-  constexpr int NKL4 = 256 / CPR;
+  constexpr int NKL4 = NT / CPR;
   constexpr int UNR = 8;   // V rows per thread in flight (and as many prefetched)
   const int c4 = tid % CPR, kl4 = tid / CPR;
   // rows past the last entry read the step's own V row (valid memory, never
@@ -211,7 +223,7 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   // visible to no query.
   const int pad = a.pad ? max(0, a.pad[bi]) : 0;
   constexpr int NSM = 16;   // logits per lane held in registers when L <= 64 * NSM
-  for (int g = w; g < G; g += 4) {
+  for (int g = w; g < G; g += NW) {
     float* pg = P + g * Lp;
     auto visible = [&](int j) { return j < L && !(pad > 0 && pos_s[min(j, L - 1)] < pad); };
     float m = kNegInf, s = 0.0f;
@@ -262,7 +274,7 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   {
     uint64_t best = ~0ull;
     int bslot = -1;
-    for (int j = tid; j < L; j += 256) {
+    for (int j = tid; j < L; j += NT) {
       float ps = 0.0f;
 #pragma unroll
       for (int g = 0; g < G; ++g) ps += prob(P[g * Lp + j], s_inv[g]);
@@ -287,7 +299,7 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   }
 
   // ---------------- 4. outputs o_g = s_inv[g] * sum_j P[g][j] v_j ----------------
-  static_assert(2 * CPR <= 256, "one thread per 16-byte chunk of the new K and V rows");
+  static_assert(2 * CPR <= NT, "one thread per 16-byte chunk of the new K and V rows");
   u32x4 nrow;   // this thread's chunk of the step's own K or V row (write back)
   {
     constexpr int NKL = NKL4;
@@ -354,10 +366,12 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   __syncthreads();
 
   // final outputs
-  for (int idx = tid; idx < G * D; idx += 256) {
+  for (int idx = tid; idx < G * D; idx += NT) {
     const int g = idx / D, d = idx - g * D;
-    const float x = (red[(0 * G + g) * D + d] + red[(1 * G + g) * D + d] +
-                     red[(2 * G + g) * D + d] + red[(3 * G + g) * D + d]) * s_inv[g];
+    float x = red[g * D + d];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) x += red[(i * G + g) * D + d];
+    x *= s_inv[g];
     E* o = static_cast<E*>(a.o) + (((int64_t)bi * a.n_heads + hk * G + g) * a.seq_ld) * D + d;
     if constexpr (BF16) {
       *o = __builtin_bit_cast(uint16_t, (__bf16)x);
@@ -372,7 +386,7 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
     uint64_t best = s_wkey[0];
     e_slot = s_wslot[0];
 #pragma unroll
-    for (int i = 1; i < 4; ++i)
+    for (int i = 1; i < NW; ++i)
       if (s_wkey[i] < best) {
         best = s_wkey[i];
         e_slot = s_wslot[i];
@@ -380,7 +394,7 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   }
   const int dst = evict ? e_slot : len0;          // slot that receives the new pair
   float* score = a.score + (int64_t)u * a.cap;
-  for (int j = tid; j < len0; j += 256)
+  for (int j = tid; j < len0; j += NT)
     if (j != dst) score[j] = sc[j];
   if (dst >= 0 && dst < len0 + (evict ? 0 : 1)) {
     E* kd = static_cast<E*>(a.kc) + ((int64_t)u * a.cap + dst) * D;
@@ -398,7 +412,7 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
     // this step's weights, summed over the group's heads: the TOVA key of the
     // next cut (the new pair's lands in its slot)
     float* lw = a.lastw + (int64_t)u * a.cap;
-    for (int j = tid; j <= len0; j += 256) {
+    for (int j = tid; j <= len0; j += NT) {
       const int slot = j < len0 ? j : dst;
       if ((j < len0 && j == dst) || slot < 0 || slot >= len0 + (evict ? 0 : 1)) continue;
       float ps = 0.0f;
@@ -410,19 +424,32 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs a) {
   if (tid == 0) a.len[u] = evict ? len0 : len0 + 1;
 }
 
+// Launches of up to one unit per compute unit take as long as one workgroup's
+// chain of loads, and eight waves shorten it: 512 bf16 entries (d = 128, G = 4)
+// 14.0 -> 12.5 us for 8 units and 16.2 -> 15.6 for 256, 2048 entries 44.9 -> 35.2,
+// 600 float32 entries 21.1 -> 14.3 for 40 units.  Sixteen waves are slower than
+// eight (13.6 and 17.8 us for the first two); so are eight for 512 units (28.2 us
+// either way in bf16, 62 -> 68 in float32) and for units of less than 32 KB of keys
+// (7.2 -> 7.6 us at 128 entries of 128 bytes).
+constexpr int kWideUnits = 256;
+constexpr size_t kWideKeyBytes = 32 << 10;
+
+template <bool BF16, int D, int G, bool NTV, int NW>
+hipError_t launch_w(const DecodeArgs& a, hipStream_t stream) {
+  const int Lp = (a.len0 + 1 + 3) & ~3;
+  const size_t lds = sizeof(float) * ((size_t)G * Lp + Lp + NW * G * D + Lp);
+  hipLaunchKernelGGL((decode_kernel<BF16, D, G, NTV, NW>), dim3((unsigned)a.units), dim3(64 * NW),
+                     lds, stream, a);
+  return hipGetLastError();
+}
+
 template <bool BF16, int D, int G>
 hipError_t launch_t(const DecodeArgs& a, hipStream_t stream) {
-  const int L = a.len0 + 1;
-  const int Lp = (L + 3) & ~3;
-  const size_t lds = sizeof(float) * ((size_t)G * Lp + Lp + 4 * G * D + Lp);
   const size_t kv_bytes = (size_t)a.units * 2 * a.len0 * D * (BF16 ? 2 : 4);
-  if (kv_bytes > kLastLevelCacheBytes)
-    hipLaunchKernelGGL((decode_kernel<BF16, D, G, true>), dim3((unsigned)a.units), dim3(256), lds,
-                       stream, a);
-  else
-    hipLaunchKernelGGL((decode_kernel<BF16, D, G, false>), dim3((unsigned)a.units), dim3(256), lds,
-                       stream, a);
-  return hipGetLastError();
+  const bool nt = kv_bytes > kLastLevelCacheBytes;
+  if (a.units <= kWideUnits && (size_t)(a.len0 + 1) * D * (BF16 ? 2 : 4) >= kWideKeyBytes)
+    return nt ? launch_w<BF16, D, G, true, 8>(a, stream) : launch_w<BF16, D, G, false, 8>(a, stream);
+  return nt ? launch_w<BF16, D, G, true, 4>(a, stream) : launch_w<BF16, D, G, false, 4>(a, stream);
 }
 
 template <bool BF16, int D>
