@@ -268,6 +268,17 @@ def make_dims(*, b, s, kv_max, block, max_gen, n_heads, n_kv_heads, head_dim, dt
 # ---------------------------------------------------------------------------
 # tensor-owning convenience wrapper
 # ---------------------------------------------------------------------------
+# the current HIP stream of a device index as an integer, without the stream
+# object that torch.cuda.current_stream makes for each call
+def _find_raw_stream():
+    import torch
+
+    return getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+_raw_stream = _find_raw_stream()
+
+
 class PDAttention:
     """Owns one layer's bounded cache (torch tensors on a GPU) and drives the ABI.
 
@@ -326,6 +337,10 @@ class PDAttention:
                               0 if self.work is None else self.work.data_ptr(),
                               0 if self.work is None else self.work_bytes)
         self.units = U
+        # for the checks of every call
+        self._dev_index = self.device.index if self.device.type == "cuda" else None
+        self._bhd = (b, n_heads, n_kv_heads, head_dim)
+        self._row_bytes = head_dim * (4 if self.dims.dtype == BM_F32 else 2)
         self.ctx = None
         # schedule settings (bm_set_*): kept here and applied again to every new
         # context, so they survive reset() and resume()
@@ -335,7 +350,29 @@ class PDAttention:
 
     # -- helpers ----------------------------------------------------------------
     def _stream(self) -> int:
+        if _raw_stream is not None and self._dev_index is not None:
+            return _raw_stream(self._dev_index)
         return self.torch.cuda.current_stream(self.device).cuda_stream
+
+    def _args_ok(self, q, k, v, o) -> bool:
+        """Whether q, k, v and o are what a call takes, checked with as few torch
+        calls as possible: the host side of a call is as long as a small step's
+        kernel (15 us a decode step with the checks one by one, 7 us like this).
+        On False the caller's own checks name what is wrong."""
+        s = q.shape
+        if len(s) != 4:
+            return False
+        b, H, Hk, d = self._bhd
+        hq, hk, dt, dev = (b, H, s[2], d), (b, Hk, s[2], d), self.tdtype, self._dev_index
+        return (s == hq and o.shape == hq and k.shape == hk and v.shape == hk
+                and q.dtype is dt and k.dtype is dt and v.dtype is dt and o.dtype is dt
+                and q.get_device() == dev and k.get_device() == dev and v.get_device() == dev
+                and o.get_device() == dev and q.is_contiguous() and k.is_contiguous()
+                and v.is_contiguous() and o.is_contiguous())
+
+    def _row_ptrs(self, q, k, v, o, row):
+        off = row * self._row_bytes
+        return q.data_ptr() + off, k.data_ptr() + off, v.data_ptr() + off, o.data_ptr() + off
 
     def _check_tensor(self, x, heads, name):
         t = self.torch
@@ -384,6 +421,9 @@ class PDAttention:
 
     def _block_args(self, t0, n_tok, q, k, v, o, row):
         row = t0 if row is None else row
+        if self._args_ok(q, k, v, o) and 0 <= row < q.shape[2] and row + n_tok <= q.shape[2]:
+            return (self.ctx, t0, n_tok, *self._row_ptrs(q, k, v, o, row), q.shape[2],
+                    self._stream())
         H, Hk = self.dims.n_heads, self.dims.n_kv_heads
         for x, hh, nm in ((q, H, "q"), (k, Hk, "k"), (v, Hk, "v"), (o, H, "o")):
             self._check_tensor(x, hh, nm)
@@ -449,6 +489,10 @@ class PDAttention:
         self._set("split", event.cuda_event)
 
     def decode_step(self, pos, q, k, v, o, row=0) -> None:
+        if self._args_ok(q, k, v, o) and 0 <= row < q.shape[2]:
+            bm_decode_step(self.ctx, pos, *self._row_ptrs(q, k, v, o, row), q.shape[2],
+                           self._stream())
+            return
         H, Hk = self.dims.n_heads, self.dims.n_kv_heads
         for x, hh, nm in ((q, H, "q"), (k, Hk, "k"), (v, Hk, "v"), (o, H, "o")):
             self._check_tensor(x, hh, nm)
