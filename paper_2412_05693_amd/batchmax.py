@@ -268,17 +268,6 @@ def make_dims(*, b, s, kv_max, block, max_gen, n_heads, n_kv_heads, head_dim, dt
 # ---------------------------------------------------------------------------
 # tensor-owning convenience wrapper
 # ---------------------------------------------------------------------------
-# the current HIP stream of a device index as an integer, without the stream
-# object that torch.cuda.current_stream makes for each call
-def _find_raw_stream():
-    import torch
-
-    return getattr(torch._C, "_cuda_getCurrentRawStream", None)
-
-
-_raw_stream = _find_raw_stream()
-
-
 class PDAttention:
     """Owns one layer's bounded cache (torch tensors on a GPU) and drives the ABI.
 
@@ -337,7 +326,9 @@ class PDAttention:
                               0 if self.work is None else self.work.data_ptr(),
                               0 if self.work is None else self.work_bytes)
         self.units = U
-        # for the checks of every call
+        # for every call's checks and stream: the current stream of a device index as an
+        # integer, without the stream object that torch.cuda.current_stream makes
+        self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         self._dev_index = self.device.index if self.device.type == "cuda" else None
         self._bhd = (b, n_heads, n_kv_heads, head_dim)
         self._row_bytes = head_dim * (4 if self.dims.dtype == BM_F32 else 2)
@@ -350,8 +341,8 @@ class PDAttention:
 
     # -- helpers ----------------------------------------------------------------
     def _stream(self) -> int:
-        if _raw_stream is not None and self._dev_index is not None:
-            return _raw_stream(self._dev_index)
+        if self._raw_stream is not None and self._dev_index is not None:
+            return self._raw_stream(self._dev_index)
         return self.torch.cuda.current_stream(self.device).cuda_stream
 
     def _args_ok(self, q, k, v, o) -> bool:

@@ -1,0 +1,157 @@
+"""GPU: sizes at the edges of the kernels' tiles, loops and dispatch rules.
+
+Against the float64 oracle under the parity protocol of the other GPU tests, or,
+where the oracle would be slow, against the same attention in float64.
+"""
+import math
+import sys
+
+import pytest
+import torch
+
+from paper_2412_05693_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+C2 = synth.WORKLOADS["c2"]
+
+
+def _parity(wl, units, **kw):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from pd_harness import run_parity
+
+    print(f"[edges] dtype={wl.dtype} b={wl.b} H={wl.n_heads}/{wl.n_kv_heads} d={wl.head_dim} "
+          f"s={wl.s} kv={wl.kv_max} B={wl.block} D={wl.n_decode} {kw}", flush=True)
+    st = run_parity(wl, synth.checked_units(wl, units), **kw)
+    print(f"[edges] -> {st.summary()}", flush=True)
+    sys.stdout.flush()
+    assert not st.failures, "\n".join(st.failures)
+
+
+@pytest.mark.parametrize("d,kv_heads", [(128, 1), (128, 4), (64, 2)], ids=["d128-G4", "d128-G1", "d64-G2"])
+@pytest.mark.parametrize("kv,block", [
+    (64, 64),      # one whole cache tile: a run of one
+    (128, 192),    # two tiles; three block tiles, so waves differ in their unmasked runs
+    (192, 65),     # three tiles; a block of one tile and one row
+    (200, 256),    # a partial cache tile between the two runs
+    (63, 127),     # a partial tile alone before the block's
+    (256, 31),     # a block shorter than a wave's rows
+], ids=lambda x: str(x))
+def test_prefill_runs_of_tiles(d, kv_heads, kv, block):
+    # runs of 0 to 5 unmasked tiles with every kind of tile behind them, in both sweeps
+    wl = C2.with_(name="edges", hh_mode="scatter", n_sinks=4, b=1, n_heads=4, n_kv_heads=kv_heads,
+                  head_dim=d, s=kv + 3 * block + 1, kv_max=kv, block=block, n_decode=0)
+    _parity(wl, wl.units, rule="tova" if kv == 192 else "ave")
+
+
+@pytest.mark.parametrize("case", [
+    # 32 KB of keys per unit is where workgroups get eight waves: 255, 256 and 257
+    # entries of 128 bytes (the cache's plus the step's)
+    dict(dtype="bf16", head_dim=64, kv_max=254),
+    dict(dtype="bf16", head_dim=64, kv_max=255),
+    dict(dtype="bf16", head_dim=64, kv_max=256),
+    # float32 keys in batches of eight rows per lane: 63, 64 and 65 entries of 512
+    # bytes (four and eight waves), a whole batch of 128 and one entry more
+    dict(dtype="f32", head_dim=128, kv_max=62),
+    dict(dtype="f32", head_dim=128, kv_max=63),
+    dict(dtype="f32", head_dim=128, kv_max=127),
+    dict(dtype="f32", head_dim=128, kv_max=128),
+    dict(dtype="f32", head_dim=64, kv_max=255),
+    dict(dtype="f32", head_dim=64, kv_max=256, n_heads=2, n_kv_heads=2),
+    # eight waves take two scores and positions per thread ahead: 1023 to 1025 entries
+    dict(dtype="bf16", head_dim=128, kv_max=1022),
+    dict(dtype="bf16", head_dim=128, kv_max=1024, n_heads=2, n_kv_heads=1),
+], ids=lambda c: "-".join(str(x) for x in c.values()))
+def test_decode_wide_workgroups(case):
+    case = {"n_heads": 4, "n_kv_heads": 1, **case}
+    wl = C2.with_(name="edges", hh_mode="scatter", n_sinks=4, b=2, s=case["kv_max"] + 40, block=128,
+                  n_decode=4, **case)
+    _parity(wl, wl.units, rule="tova" if case["kv_max"] == 256 else "ave")
+
+
+@pytest.mark.parametrize("b", [256, 257])
+def test_decode_units_at_the_wide_limit(b):
+    wl = C2.with_(name="edges", hh_mode="scatter", n_sinks=4, b=b, n_heads=4, n_kv_heads=1,
+                  head_dim=128, s=200, kv_max=160, block=64, n_decode=3)
+    _parity(wl, 4)
+
+
+@pytest.mark.parametrize("dtype,d,group,b,n", [
+    ("bf16", 128, 4, 1, 4608),     # chunks of 512 keys: nine whole ones and the step's key
+    ("bf16", 128, 1, 2, 4607),     # nine whole ones with it
+    ("bf16", 64, 2, 1, 65400),     # the longest cache: 128 chunks
+    ("f32", 128, 2, 1, 5001),
+    ("f32", 64, 4, 1, 20000),
+    ("bf16", 128, 4, 64, 8200),    # 269 MB of rows: past the last-level cache
+    ("f32", 64, 1, 128, 4200),     # 275 MB
+], ids=lambda x: str(x))
+def test_long_decode_chunks(dtype, d, group, b, n):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2412_05693_amd.batchmax import PDAttention
+
+    print(f"[edges] long {dtype} d={d} G={group} b={b} n={n}", flush=True)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda", dtype=dt)
+
+    att = PDAttention(b=b, s=n, kv_max=n + 8, block=64, max_gen=1 << 20, n_heads=group,
+                      n_kv_heads=1, head_dim=d, dtype=dtype)
+    att.set_rank_rule("recent")
+    att.set_score_accumulation(False)
+    k, v = normal(b, 1, n, d), normal(b, 1, n, d)
+    k[:, :, ::97] *= 3                      # maxima that differ from chunk to chunk
+    att.k[:, :, :n], att.v[:, :, :n] = k, v
+    att.pos[:, :, :n] = torch.arange(n, device="cuda", dtype=torch.int32)
+    att.score.zero_()
+    att.len.fill_(n)
+    att.resume(n, n)
+    q, kn, vn = normal(b, group, 1, d), normal(b, 1, 1, d), normal(b, 1, 1, d)
+    o = torch.empty_like(q)
+    att.decode_step(n, q, kn, vn, o)
+    kk = torch.cat([k, kn], dim=2)
+    vv = torch.cat([v, vn], dim=2)
+    # float64 one sample at a time; elementwise products, so that no batched matrix
+    # product runs
+    for i in range(b):
+        z = (q[i].double() * kk[i].double()).sum(-1) if group == 1 else torch.stack(
+            [(q[i, j].double() * kk[i, 0].double()).sum(-1) for j in range(group)])
+        p = torch.softmax(z / math.sqrt(d), dim=-1)
+        ref = torch.stack([(p[j][:, None] * vv[i, 0].double()).sum(0) for j in range(group)])
+        err = (o[i, :, 0].double() - ref).abs().max().item()
+        # bf16: the output's rounding, 2^-9 relative, and as much again for the rounding
+        # of weights or inputs to it; float32: some thousand roundings of 2^-24 each, most
+        # of which cancel; both relative to the largest output
+        tol = (2.0 ** -8 if dtype == "bf16" else 1e-5) * ref.abs().max().item()
+        assert err <= tol, f"sample {i}: {err:.3e} > {tol:.3e}"
+    assert torch.equal(att.k[:, :, n:n + 1], kn) and torch.equal(att.v[:, :, n:n + 1], vn)
+    assert bool((att.pos[:, :, n] == n).all()) and bool((att.len == n + 1).all())
+    att.close()
+
+
+@pytest.mark.parametrize("what", ["shape", "dtype", "stride", "device", "rows", "row"])
+def test_calls_that_are_refused(what):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2412_05693_amd.batchmax import PDAttention
+
+    att = PDAttention(b=1, s=64, kv_max=32, block=32, max_gen=4, n_heads=2, n_kv_heads=1, head_dim=64)
+    q = torch.zeros((1, 2, 32, 64), device="cuda", dtype=torch.bfloat16)
+    good = {"q": q, "k": q[:, :1].clone(), "v": q[:, :1].clone(), "o": torch.empty_like(q)}
+    bad = {"shape": lambda x: x[:, :, :, :32].contiguous(), "dtype": lambda x: x.float(),
+           "stride": lambda x: x.transpose(2, 3).contiguous().transpose(2, 3),
+           "device": lambda x: x.cpu(), "rows": lambda x: torch.cat([x, x], dim=2),
+           "row": lambda x: x}[what]
+    for name in good:
+        args = {**good, name: bad(good[name])}
+        row = 32 if what == "row" else 0
+        with pytest.raises(ValueError):
+            att.prefill_block(0, 32, **args, row=row)
+        with pytest.raises(ValueError):
+            att.decode_step(0, **args, row=row)
+    att.prefill_block(0, 32, **good, row=0)
+    torch.cuda.synchronize()
+    att.close()
