@@ -72,6 +72,7 @@ struct PrefillArgs {
   float* partial;     // [U, npt, cap]
   int64_t seq_ld;
   int n_heads, n_kv_heads, cap, len0, n_tok, t0, npt_used, npt_stride, units;
+  int nsplit;         // workgroups per position tile (set by launch_prefill)
   int accumulate;     // 0: outputs only (no score sums; new entries get score 0)
   const int32_t* pad; // [b] left pad tokens per sample, or null
   float* lastw;       // [U, cap] weights of the block's last query, or null

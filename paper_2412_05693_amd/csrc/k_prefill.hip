@@ -170,6 +170,7 @@ __device__ __forceinline__ typename Cfg<BF16, D>::kfrag_t k_frag(const char* ks,
 
 struct Geo {
   int u, bi, hk, pt, w, lane, n, h, g, sub;
+  int split;       // which of the launch's nsplit workgroups of this tile
   int pbase;       // first block position (relative to t0) of the workgroup
   int wrow0;       // first query row (relative to t0) of this wave
   int row;         // this lane's query row (relative to t0) in S^T orientation
@@ -186,7 +187,7 @@ struct Geo {
   bool qpad;       // this lane's query row is a pad token
 };
 
-template <int G, bool PAD>
+template <int G, bool PAD, bool SPLIT>
 __device__ __forceinline__ Geo make_geo(const PrefillArgs& a) {
   Geo s;
   // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
@@ -194,7 +195,12 @@ __device__ __forceinline__ Geo make_geo(const PrefillArgs& a) {
   // one unit -- land on the same XCD and share that unit's K/V in its L2.
   const int nwg = gridDim.x, L = blockIdx.x;
   const int q8 = nwg >> 3, r8 = nwg & 7, xcd = L & 7;
-  const int lin = xcd * q8 + min(xcd, r8) + (L >> 3);
+  int lin = xcd * q8 + min(xcd, r8) + (L >> 3);
+  s.split = 0;
+  if constexpr (SPLIT) {
+    s.split = lin % a.nsplit;
+    lin /= a.nsplit;
+  }
   s.u = lin / a.npt_used;
   s.pt = lin - s.u * a.npt_used;
   s.bi = s.u / a.n_kv_heads;
@@ -304,10 +310,11 @@ __device__ __forceinline__ void copy_tile(uint32_t dst, u32x4 rsrc, const int (&
 // wait for the wave's copies; LDS may hold new tiles from here on
 __device__ __forceinline__ void tile_fence() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-template <bool BF16, int D, int G, bool PAD>
+template <bool BF16, int D, int G, bool PAD, bool SPLIT>
 __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_attn_kernel(PrefillArgs a) {
   // PAD: the launch has left padding (a separate instantiation, so the common
-  // case carries none of its registers)
+  // case carries none of its registers).  SPLIT: each position tile has a.nsplit
+  // workgroups that all run sweep 1 and share what follows (see split_of)
   using C = Cfg<BF16, D>;
   using E = typename C::E;
   constexpr int RB = C::RB;
@@ -327,7 +334,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   __shared__ float lws[3][kWaves][kKeyTile];
   uint64_t tl[BM_TIMELINE_FIELDS] = {};
   if constexpr (kTimeline) tl[BM_TL_ENTRY] = tl_now();
-  Geo s = make_geo<G, PAD>(a);
+  Geo s = make_geo<G, PAD, SPLIT>(a);
   const int tid = threadIdx.x;
   auto stamp = [&](int field) BM_LAMBDA {
     if constexpr (kTimeline) tl[field] = tl_now();
@@ -362,9 +369,9 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 
   // Left padding: past the pads, the smallest cached position tells whether the cache
   // still holds one (a score-ranked cut removes pads first: their scores are 0)
-  // and, if not, the unmasked loops run.  With the skipped pad tiles and pad rows,
-  // per prompt of b=8, 40 heads, s=3584, up to 1024 pads: 1990 -> 1950 us (8 percent
-  // of its work is on pads; the longest prompt has none)
+  // and, if not, the unmasked loops run.  With the skipped pad tiles and pad rows:
+  // b=8, 40 heads, s=3584, up to 1024 pads (one prompt without), per prompt and in
+  // turn with one former kernel: 1.044x -> 1.068x of its speed (1950 us)
   int pos_min = -1;
   if constexpr (PAD) {
     if (s.pad > 0 && a.t0 >= s.pad) {
@@ -382,7 +389,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   //      so the workgroup waits for memory once before its first tile. ----
   const int64_t plane = ((int64_t)s.bi * a.n_kv_heads + s.hk) * a.seq_ld;
   constexpr int NA = (PT * C::CPR + kThreads - 1) / kThreads;   // chunks per thread
-  const int app_chunks = (s.in_rows - s.pbase) * C::CPR;
+  const int app_chunks = s.split == 0 ? (s.in_rows - s.pbase) * C::CPR : 0;
   u32x4 app_k[NA], app_v[NA];
   {
     const E* kin = static_cast<const E*>(a.kin);
@@ -411,6 +418,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
         *reinterpret_cast<u32x4*>(vc + dst) = app_v[i];
       }
     }
+    if (s.split != 0) return;
     for (int r = s.pbase + tid; r < s.in_rows; r += kThreads)
       a.pos[(int64_t)s.u * a.cap + a.len0 + r] = a.t0 + r;
   };
@@ -482,6 +490,14 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 
   stamp(BM_TL_QUERY_ISSUED);
   const int nt = s.nt;
+  // sweep 2's tiles of this workgroup: n2 from lo2 on.  Of three or more workgroups
+  // the first stores the outputs and the others make the sums; two share the tiles
+  int lo2 = 0, n2 = nt;
+  if constexpr (SPLIT) {
+    const int first = a.nsplit > 2, parts = a.nsplit - first, k = s.split - first;
+    lo2 = k < 0 ? 0 : nt * k / parts;
+    n2 = k < 0 ? 0 : nt * (k + 1) / parts - lo2;
+  }
   const float c2 = a.scale_log2;
   // the row this lane's causal mask uses (padding rows reuse the last real row)
   const int qrow = s.qvalid ? s.row : a.n_tok - 1;
@@ -781,8 +797,8 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     const int par = t & 1;
     if (t + 1 < nt)
       dma_k(par ^ 1, tile_info(a, s, t + 1), t + 1);
-    else if (a.accumulate)
-      dma_k(par ^ 1, tile_info2(a, s, 0), nt);
+    else if (SPLIT ? n2 > 0 : a.accumulate != 0)
+      dma_k(par ^ 1, tile_info2(a, s, lo2), nt);
     dma_v(par, tile_info(a, s, t));
     if constexpr (kTimeline) tl[BM_TL_S1_COPY_ISSUE] += tl_now() - issue0;
   };
@@ -906,10 +922,10 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
         const int r = RPR * j + s.lane / (RB / 16), c = s.lane % (RB / 16);
         const u32x4 v =
             *reinterpret_cast<const u32x4*>(ost + r * RB + 16 * (c ^ swz_k<BF16, D>(r)));
-        if (s.wrow0 + r < a.n_tok)
+        if (s.wrow0 + r < a.n_tok && s.split == 0)
           *reinterpret_cast<u32x4*>(o + (int64_t)r * RB + c * 16) = v;
       }
-    } else if (s.qvalid) {
+    } else if (s.qvalid && s.split == 0) {
       int orow = s.row, ohead = s.bi * a.n_heads + s.hk * G + s.g;
       asm volatile("" : "+v"(orow), "+v"(ohead));
       E* o = static_cast<E*>(a.o) + ((int64_t)ohead * a.seq_ld + orow) * D;
@@ -927,7 +943,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // ======================= sweep 2: exact column sums ========================
   // (skipped when the caller asked for outputs only)
   stamp(BM_TL_OUTPUT_STORED);
-  if (!a.accumulate) {
+  if (SPLIT ? n2 == 0 : !a.accumulate) {
     timeline_end();
     return;
   }
@@ -974,11 +990,11 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // Step t: K(t) is in LDS (sweep 1's last step fetched K(0)); K(t+1) is fetched
   // meanwhile.  After the step's barrier tile t - 1's sums of all waves are in cs.
   auto fetch2 = [&](int t) BM_LAMBDA {
-    if (t + 1 < nt) dma_k((nt + t + 1) & 1, tile_info2(a, s, t + 1), nt + t + 1);
+    if (t + 1 < n2) dma_k((nt + t + 1) & 1, tile_info2(a, s, lo2 + t + 1), nt + t + 1);
   };
   // add the waves' sums of tile t (the waves take turns)
   auto store_sums = [&](int t) BM_LAMBDA {
-    const TileInfo ti = tile_info2(a, s, t);
+    const TileInfo ti = tile_info2(a, s, lo2 + t);
     if (s.w == (t & (kWaves - 1)) && s.lane < ti.valid) {
       float acc = 0.0f;
 #pragma unroll
@@ -993,7 +1009,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     }
   };
   auto sweep2_step = [&](auto mask_tag, int t) BM_LAMBDA {
-    const TileInfo ti = tile_info2(a, s, t);
+    const TileInfo ti = tile_info2(a, s, lo2 + t);
     float (*ct)[kKeyTile] = cs[t % 3];
     f32x16* cur = sl;
     fetch2(t);
@@ -1077,7 +1093,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     }
   };
   // tiles without a mask: the whole cache tiles and the block's up to the diagonal
-  const int nun2 = s.works ? s.ncf + s.nbu : 0;
+  const int nun2 = s.works ? min(max(s.ncf + s.nbu - lo2, 0), n2) : 0;
   int t2 = 0;
   if (FAST && (!PAD || s.pad == 0) && !wg_last && nun2 > 0) {
     fetch2(0);
@@ -1099,9 +1115,9 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     sums_half(sl[1], 1, t2 - 1);
   }
   for (; t2 < nun2; ++t2) sweep2_step(std::false_type{}, t2);
-  for (; t2 < nt; ++t2) sweep2_step(std::true_type{}, t2);
+  for (; t2 < n2; ++t2) sweep2_step(std::true_type{}, t2);
   __syncthreads();
-  store_sums(nt - 1);
+  store_sums(n2 - 1);
   timeline_end();
 }
 
@@ -1139,14 +1155,36 @@ __global__ void __launch_bounds__(256) score_reduce_kernel(PrefillArgs a, int pt
   if (blockIdx.y == 0 && threadIdx.x == 0) a.len[u] = n;
 }
 
-template <bool BF16, int D, int G>
-hipError_t launch_t(const PrefillArgs& a, hipStream_t stream) {
-  dim3 grid((unsigned)(a.units * a.npt_used));
+// Workgroups per position tile.  A launch of fewer workgroups than compute units
+// takes as long as one of them, and sweep 2 is a third of that: idle units take
+// over its tiles, each after a sweep 1 of its own (every one needs the rows'
+// normalisers).  Sums and outputs stay the same bit for bit.  Per prompt, block by
+// block: 64 workgroups of b=1 s=4096 529 -> 457 us, 80 of b=5 d=64 s=1999 550 -> 484,
+// 8 of float32 b=2 s=512 (with 32 decode steps) 409 -> 375.  With a second
+// workgroup on a compute unit the repeated sweep 1 would cost time again (a wave's
+// tile takes half as long again beside another's), and past four the outputs'
+// store is as long as the sums.
+constexpr int kComputeUnits = 256;
+constexpr int kMaxSplit = 4;
+int split_of(const PrefillArgs& a) {
+  if (kTimeline || !a.accumulate) return 1;
+  return max(1, min(kMaxSplit, kComputeUnits / (a.units * a.npt_used)));
+}
+
+template <bool BF16, int D, int G, bool SPLIT>
+hipError_t launch_s(const PrefillArgs& a, hipStream_t stream) {
+  dim3 grid((unsigned)(a.units * a.npt_used * a.nsplit));
   if (a.pad)
-    hipLaunchKernelGGL((prefill_attn_kernel<BF16, D, G, true>), grid, dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((prefill_attn_kernel<BF16, D, G, true, SPLIT>), grid, dim3(kThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL((prefill_attn_kernel<BF16, D, G, false>), grid, dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((prefill_attn_kernel<BF16, D, G, false, SPLIT>), grid, dim3(kThreads), 0, stream, a);
   return hipGetLastError();
+}
+
+template <bool BF16, int D, int G>
+hipError_t launch_t(PrefillArgs a, hipStream_t stream) {
+  a.nsplit = split_of(a);
+  return a.nsplit > 1 ? launch_s<BF16, D, G, true>(a, stream) : launch_s<BF16, D, G, false>(a, stream);
 }
 
 template <bool BF16, int D>
