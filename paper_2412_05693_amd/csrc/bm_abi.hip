@@ -425,6 +425,14 @@ int check_rule(const bm_ctx* ctx) {
   return BM_OK;
 }
 
+// Cuts of up to this many bytes of moved rows per unit go through one launch, whose
+// one workgroup per unit also moves the rows; more rows are moved by a launch of
+// their own with many workgroups per unit.  40 units of 433 entries, up to 100 rows of
+// 256 bytes: 5.2 + 4.5 us in two launches; s=1999 in blocks of 100 with such cuts
+// 484 -> 464 us.  One workgroup moves 16 KB per round of its loads, so the limit is
+// four rounds, about as long as the launch that is saved.
+constexpr int64_t kOneLaunchMoveBytes = 64 << 10;
+
 // Enqueue the cut of every unit from ctx->len down to `target` entries (select
 // + compaction), ranked at curr_id.  Requires ctx->len > target; the caller has
 // checked the rule.
@@ -447,10 +455,18 @@ int cut_to(bm_ctx* ctx, int target, int32_t curr_id, hipStream_t stream) {
   a.elem_bytes = ctx->elem_bytes;
   a.rule = ctx->rule;
   a.lastw = reinterpret_cast<float*>(work_at(ctx, ctx->lay.lastw_off));
-  hipError_t e = bm::launch_select(a, stream);
-  if (e != hipSuccess) return hip_fail(e, "select launch");
   const int n_evict = ctx->len - target;
   const int max_moves = n_evict < target ? n_evict : target;
+  hipError_t e;
+  if (a.n <= bm::kMaxCap &&
+      (int64_t)max_moves * 2 * a.head_dim * a.elem_bytes <= kOneLaunchMoveBytes) {
+    e = bm::launch_cut(a, stream);
+    if (e != hipSuccess) return hip_fail(e, "cut launch");
+    ctx->len = target;
+    return BM_OK;
+  }
+  e = bm::launch_select(a, stream);
+  if (e != hipSuccess) return hip_fail(e, "select launch");
   if (max_moves > 0) {
     e = bm::launch_compact(a, max_moves, stream);
     if (e != hipSuccess) return hip_fail(e, "compact launch");

@@ -144,6 +144,8 @@ hipError_t launch_score_reduce(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_select(const EvictArgs& a, hipStream_t stream);
 hipError_t launch_fold_cut(const PrefillArgs& pa, const EvictArgs& a, int pt_positions,
                            hipStream_t stream);
+// select and compaction of a.n <= kMaxCap entries in one launch
+hipError_t launch_cut(const EvictArgs& a, hipStream_t stream);
 hipError_t launch_compact(const EvictArgs& a, int max_moves, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, int head_dim, int group,
                          hipStream_t stream);

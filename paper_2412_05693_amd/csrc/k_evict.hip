@@ -295,8 +295,9 @@ __global__ void __launch_bounds__(256) compact_kernel(EvictArgs a, int nchunks) 
 // three).  The folded scores, the positions and TOVA's weights stay in LDS, the
 // keys in registers; the hole and source lists are built in LDS; the moves copy
 // K and V rows with 16-byte loads and stores.  Needs n <= kMaxCap.
-// KP: keys per thread held in registers (n <= 256 KP)
-template <int KP>
+// KP: keys per thread held in registers (n <= 256 KP).  FOLD: off for a cut by
+// itself, whose scores are complete
+template <int KP, bool FOLD>
 __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs a,
                                                         int pt_positions) {
   __shared__ uint32_t hist[512];
@@ -332,7 +333,7 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
   static_assert(KP % FK == 0, "whole rounds");
   uint64_t key[KP];
   const int nlast = n - 1;
-  const int npt_used = pa.accumulate ? pa.npt_used : 0;
+  const int npt_used = FOLD && pa.accumulate ? pa.npt_used : 0;
 #pragma unroll
   for (int i0 = 0; i0 < KP; i0 += FK) {
     if (i0 >= per) break;   // uniform across the workgroup
@@ -364,18 +365,18 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
 #pragma unroll
     for (int f = 0; f < FK; ++f) {
       const int jc = min(tid + 256 * (i0 + f), nlast);
-      pt0[f] = jc < pa.len0 ? 0 : (jc - pa.len0) / pt_positions;
+      pt0[f] = !FOLD || jc < pa.len0 ? 0 : (jc - pa.len0) / pt_positions;
       sc0[f] = score[jc];
       p[f] = pos[jc];
       l[f] = last ? last[jc] : 0.0f;
     }
-    load_terms(0);   // issued with the loads above, before any of them is used
+    if constexpr (FOLD) load_terms(0);   // issued with the loads above, before any of them is used
 #pragma unroll
     for (int f = 0; f < FK; ++f) {
       const int jc = min(tid + 256 * (i0 + f), nlast);
-      acc[f] = jc < pa.len0 ? sc0[f] : 0.0f;
+      acc[f] = !FOLD || jc < pa.len0 ? sc0[f] : 0.0f;
     }
-    add_terms(0);
+    if constexpr (FOLD) add_terms(0);
     for (int c0 = PTC; c0 < npt_used; c0 += PTC) {
       load_terms(c0);
       add_terms(c0);
@@ -385,7 +386,7 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
       const int i = i0 + f, j = tid + 256 * i;
       key[i] = ~0ull;
       if (i < per && j < n) {
-        score[j] = acc[f];
+        if constexpr (FOLD) score[j] = acc[f];
         sc[j] = acc[f];
         ps[j] = p[f];
         lw[j] = l[f];
@@ -416,14 +417,26 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
   const int cpr = row_bytes / 16;
   char* kc = static_cast<char*>(a.kc) + (int64_t)u * a.cap * row_bytes;
   char* vc = static_cast<char*>(a.vc) + (int64_t)u * a.cap * row_bytes;
-  for (int c = tid; c < m * 2 * cpr; c += 256) {
-    const int mv = c / (2 * cpr);
-    const int rem = c - mv * 2 * cpr;
-    const int which = rem / cpr, cc = rem - which * cpr;
-    char* base = which ? vc : kc;
-    const int64_t src = (int64_t)srcs[mv] * row_bytes + cc * 16;
-    const int64_t dst = (int64_t)holes[mv] * row_bytes + cc * 16;
-    *reinterpret_cast<uint4*>(base + dst) = *reinterpret_cast<const uint4*>(base + src);
+  // four loads in flight per thread: a chunk's store would otherwise wait for its
+  // load before the next load goes out (sources and holes share no slot)
+  constexpr int UM = 4;
+  const int chunks = m * 2 * cpr;
+  for (int c0 = tid; c0 < chunks; c0 += 256 * UM) {
+    uint4 x[UM];
+    char* to[UM];
+#pragma unroll
+    for (int i = 0; i < UM; ++i) {
+      const int c = min(c0 + 256 * i, chunks - 1);
+      const int mv = c / (2 * cpr);
+      const int rem = c - mv * 2 * cpr;
+      const int which = rem / cpr, cc = rem - which * cpr;
+      char* base = (which ? vc : kc) + cc * 16;
+      x[i] = *reinterpret_cast<const uint4*>(base + (int64_t)srcs[mv] * row_bytes);
+      to[i] = base + (int64_t)holes[mv] * row_bytes;
+    }
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+      if (c0 + 256 * i < chunks) *reinterpret_cast<uint4*>(to[i]) = x[i];
   }
   for (int mv = tid; mv < m; mv += 256) {
     const int sj = srcs[mv], dj = holes[mv];
@@ -436,20 +449,32 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
 
 }  // namespace
 
-hipError_t launch_fold_cut(const PrefillArgs& pa, const EvictArgs& a, int pt_positions,
-                           hipStream_t stream) {
+namespace {
+
+template <bool FOLD>
+hipError_t launch_cut_t(const PrefillArgs& pa, const EvictArgs& a, int pt_positions, hipStream_t stream) {
   if (a.n > kMaxCap) return hipErrorInvalidValue;
   const size_t lds = 5 * sizeof(int32_t) * (size_t)((a.n + 3) & ~3);
+  const dim3 grid((unsigned)a.units);
   if (a.n <= 256 * 3)
-    hipLaunchKernelGGL(fold_cut_kernel<3>, dim3((unsigned)a.units), dim3(256), lds, stream, pa, a,
-                       pt_positions);
+    hipLaunchKernelGGL((fold_cut_kernel<3, FOLD>), grid, dim3(256), lds, stream, pa, a, pt_positions);
   else if (a.n <= 256 * 4)
-    hipLaunchKernelGGL(fold_cut_kernel<4>, dim3((unsigned)a.units), dim3(256), lds, stream, pa, a,
-                       pt_positions);
+    hipLaunchKernelGGL((fold_cut_kernel<4, FOLD>), grid, dim3(256), lds, stream, pa, a, pt_positions);
   else
-    hipLaunchKernelGGL(fold_cut_kernel<kMaxPer>, dim3((unsigned)a.units), dim3(256), lds, stream, pa,
-                       a, pt_positions);
+    hipLaunchKernelGGL((fold_cut_kernel<kMaxPer, FOLD>), grid, dim3(256), lds, stream, pa, a,
+                       pt_positions);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_fold_cut(const PrefillArgs& pa, const EvictArgs& a, int pt_positions,
+                           hipStream_t stream) {
+  return launch_cut_t<true>(pa, a, pt_positions, stream);
+}
+
+hipError_t launch_cut(const EvictArgs& a, hipStream_t stream) {
+  return launch_cut_t<false>(PrefillArgs{}, a, 1, stream);
 }
 
 hipError_t launch_select(const EvictArgs& a, hipStream_t stream) {

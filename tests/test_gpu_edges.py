@@ -36,6 +36,7 @@ def _parity(wl, units, **kw):
     (192, 65),     # three tiles; a block of one tile and one row
     (200, 256),    # a partial cache tile between the two runs
     (63, 127),     # a partial tile alone before the block's
+    (160, 128), (160, 129),   # the most rows that a cut by itself moves in one launch, and one more
     (256, 31),     # a block shorter than a wave's rows
 ], ids=lambda x: str(x))
 def test_prefill_runs_of_tiles(d, kv_heads, kv, block):
