@@ -3,8 +3,9 @@
 //
 // Decode is bandwidth-bound (the paper notes it reloads the whole cache every
 // step, Sec. 1): the kernel reads each cached K and V row exactly once.  One
-// workgroup of four or eight waves per unit (sample, KV head); L = len + 1 entries (len cached slots
-// plus the step's pair, which sits in a virtual slot `len`).
+// workgroup of four or eight waves per unit (sample, KV head); L = len + 1
+// entries (len cached slots plus the step's pair, which sits in a virtual slot
+// `len`).
 //   1. logits z[g][j] = sm_scale * q_g . k_j for the G query heads, kept in LDS
 //      (bf16: a 16x16x32 MFMA per 16 keys, K rows as the A operand straight
 //      from global memory; f32: VALU dot products);

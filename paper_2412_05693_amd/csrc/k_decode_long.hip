@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(256) decode_split_kernel(LongDecodeArgs a) {
 // One workgroup per (unit, query head): 256 / D groups of D threads take every
 // 256 / D-th chunk, so a head's partials are read with many loads in flight (one
 // workgroup per unit, each thread walking all chunks twice, took 19 us for 64
-// units of 17 chunks against 48 us for the split itself).
+// units of 17 chunks against 48 us for the split itself; 4.7 us like this).
 template <bool BF16, int D, int G>
 __global__ void __launch_bounds__(256) decode_combine_kernel(LongDecodeArgs a) {
   using E = typename std::conditional<BF16, uint16_t, float>::type;
