@@ -40,6 +40,7 @@ using lanes::wave_sum;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 constexpr float kNegInf = -__builtin_huge_valf();
 
@@ -51,22 +52,32 @@ __device__ __forceinline__ float prob(float e, float inv) {
   return e * inv;
 }
 
-template <bool NT>
-__device__ __forceinline__ u32x4 load_v(const void* p) {
+template <bool NT, typename V>
+__device__ __forceinline__ V load_v(const void* p) {
   if constexpr (NT) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
   } else {
-    return *reinterpret_cast<const u32x4*>(p);
+    return *reinterpret_cast<const V*>(p);
   }
 }
 
-// NW: waves per workgroup
+// NW: waves per workgroup, four or eight.  A launch chooses them by its number of
+// units, so both add the same terms in the same order and a sample's results are the
+// same bits in any batch.  That matters for the outputs alone (logits belong to one
+// MFMA or one lane group each, softmax sums to one wave): eight waves take V rows 8
+// bytes a lane instead of 16, so twice the threads stand for the same rows, and their
+// eight partial sums are added in pairs first.
 template <bool BF16, int D, int G, bool NTV, int NW>
 __global__ void __launch_bounds__(64 * NW) decode_kernel(DecodeArgs a) {
   constexpr int NT = 64 * NW;               // threads
   using E = typename std::conditional<BF16, uint16_t, float>::type;
   constexpr int EPC = 16 / sizeof(E);       // elements per 16-byte chunk
   constexpr int CPR = D / EPC;              // 16-byte chunks per row
+  static_assert(NW == 4 || NW == 8, "four or eight waves");
+  constexpr int VDW = NW == 4 ? 4 : 2;      // dwords of a V row per lane
+  using vchunk_t = typename std::conditional<NW == 4, u32x4, u32x2>::type;
+  constexpr int EPV = 4 * VDW / (int)sizeof(E);   // elements of a V row per lane
+  constexpr int CPV = D / EPV;              // lanes per V row
   extern __shared__ float dsm[];
   __shared__ uint64_t s_wkey[NW];
   __shared__ int s_wslot[NW];
@@ -205,16 +216,16 @@ __global__ void __launch_bounds__(64 * NW) decode_kernel(DecodeArgs a) {
   __syncthreads();
 
   // first batch of V rows for phase 4, in flight during the softmax
-  constexpr int NKL4 = NT / CPR;
+  constexpr int NKL4 = NT / CPV;
   constexpr int UNR = 8;   // V rows per thread in flight (and as many prefetched)
-  const int c4 = tid % CPR, kl4 = tid / CPR;
+  const int c4 = tid % CPV, kl4 = tid / CPV;
   // rows past the last entry read the step's own V row (valid memory, never
   // used): unconditional loads, so only the batch being consumed is waited for
-  auto v_row = [&](int j) -> u32x4 {
+  auto v_row = [&](int j) -> vchunk_t {
     const E* src = j < len0 ? vc + (int64_t)j * D : vnew;
-    return load_v<NTV>(src + c4 * EPC);
+    return load_v<NTV, vchunk_t>(src + c4 * EPV);
   };
-  u32x4 vw[UNR];
+  vchunk_t vw[UNR];
 #pragma unroll
   for (int r = 0; r < UNR; ++r) vw[r] = v_row(kl4 + r * NKL4);
 
@@ -305,38 +316,46 @@ __global__ void __launch_bounds__(64 * NW) decode_kernel(DecodeArgs a) {
   {
     constexpr int NKL = NKL4;
     const int c = c4;
-    float acc[G][EPC];
+    float acc[G][EPV];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-      for (int e = 0; e < EPC; ++e) acc[g][e] = 0.0f;
+      for (int e = 0; e < EPV; ++e) acc[g][e] = 0.0f;
     for (int j0 = kl4; j0 < L; j0 += NKL * UNR) {
       // next batch in flight while this one is consumed
-      u32x4 vn[UNR];
+      vchunk_t vn[UNR];
 #pragma unroll
       for (int r = 0; r < UNR; ++r) vn[r] = v_row(j0 + (UNR + r) * NKL);
+      // a whole batch has no test between its rows, so its probabilities are read
+      // together (512 float32 entries in 8 units, with eight waves: 23.2 -> 22.0 us)
+      auto add_batch = [&](auto whole) {
 #pragma unroll
-      for (int r = 0; r < UNR; ++r) {
-        const int j = j0 + r * NKL;
-        if (j >= L) break;
-        float vf[EPC];
-        if constexpr (BF16) {
+        for (int r = 0; r < UNR; ++r) {
+          const int j = j0 + r * NKL;
+          if (!decltype(whole)::value && j >= L) break;
+          float vf[EPV];
+          if constexpr (BF16) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            vf[2 * e] = __uint_as_float(vw[r][e] << 16);
-            vf[2 * e + 1] = __uint_as_float(vw[r][e] & 0xffff0000u);
+            for (int e = 0; e < VDW; ++e) {
+              vf[2 * e] = __uint_as_float(vw[r][e] << 16);
+              vf[2 * e + 1] = __uint_as_float(vw[r][e] & 0xffff0000u);
+            }
+          } else {
+#pragma unroll
+            for (int e = 0; e < VDW; ++e) vf[e] = __uint_as_float(vw[r][e]);
           }
-        } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) vf[e] = __uint_as_float(vw[r][e]);
+          for (int g = 0; g < G; ++g) {
+            const float p = P[g * Lp + j];
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) acc[g][e] = fmaf(p, vf[e], acc[g][e]);
+          }
         }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const float p = P[g * Lp + j];
-#pragma unroll
-          for (int e = 0; e < EPC; ++e) acc[g][e] = fmaf(p, vf[e], acc[g][e]);
-        }
-      }
+      };
+      if (j0 + (UNR - 1) * NKL < L)
+        add_batch(std::true_type{});
+      else
+        add_batch(std::false_type{});
 #pragma unroll
       for (int r = 0; r < UNR; ++r) vw[r] = vn[r];
     }
@@ -345,23 +364,24 @@ __global__ void __launch_bounds__(64 * NW) decode_kernel(DecodeArgs a) {
       const int nc = min(tid, 2 * CPR - 1);
       nrow = *reinterpret_cast<const u32x4*>((nc >= CPR ? vnew : knew) + (nc % CPR) * EPC);
     }
-    // reduce the lanes of a wave that share chunk c (lanes c, c + CPR, ...),
+    // reduce the lanes of a wave that share chunk c (lanes c, c + CPV, ...),
     // then across waves in LDS
-    static_assert(CPR == 8 || CPR == 16 || CPR == 32, "16-byte chunks per row");
+    static_assert(CPV == 8 || CPV == 16 || CPV == 32 || CPV == 64, "lanes per row");
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-      for (int e = 0; e < EPC; ++e) {
+      for (int e = 0; e < EPV; ++e) {
         float x = acc[g][e];
-        if constexpr (CPR <= 8) x = add_xor<8>(x);
-        if constexpr (CPR <= 16) x = add_xor<16>(x);
-        acc[g][e] = add_xor<32>(x);
+        if constexpr (CPV <= 8) x = add_xor<8>(x);
+        if constexpr (CPV <= 16) x = add_xor<16>(x);
+        if constexpr (CPV <= 32) x = add_xor<32>(x);
+        acc[g][e] = x;
       }
-    if (lane < CPR) {
+    if (lane < CPV) {
 #pragma unroll
       for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) red[(w * G + g) * D + c * EPC + e] = acc[g][e];
+        for (int e = 0; e < EPV; ++e) red[(w * G + g) * D + c * EPV + e] = acc[g][e];
     }
   }
   __syncthreads();
@@ -369,9 +389,14 @@ __global__ void __launch_bounds__(64 * NW) decode_kernel(DecodeArgs a) {
   // final outputs
   for (int idx = tid; idx < G * D; idx += NT) {
     const int g = idx / D, d = idx - g * D;
-    float x = red[g * D + d];
+    // the sum of four waves' rows: one wave's partial, or the pair's
+    auto part = [&](int i) {
+      if constexpr (NW == 4) return red[(i * G + g) * D + d];
+      else return red[(2 * i * G + g) * D + d] + red[((2 * i + 1) * G + g) * D + d];
+    };
+    float x = part(0);
 #pragma unroll
-    for (int i = 1; i < NW; ++i) x += red[(i * G + g) * D + d];
+    for (int i = 1; i < 4; ++i) x += part(i);
     x *= s_inv[g];
     E* o = static_cast<E*>(a.o) + (((int64_t)bi * a.n_heads + hk * G + g) * a.seq_ld) * D + d;
     if constexpr (BF16) {
@@ -426,12 +451,17 @@ __global__ void __launch_bounds__(64 * NW) decode_kernel(DecodeArgs a) {
 }
 
 // Launches of up to one unit per compute unit take as long as one workgroup's
-// chain of loads, and eight waves shorten it: 512 bf16 entries (d = 128, G = 4)
-// 14.0 -> 12.5 us for 8 units and 16.2 -> 15.6 for 256, 2048 entries 44.9 -> 35.2,
-// 600 float32 entries 21.1 -> 14.3 for 40 units.  Sixteen waves are slower than
-// eight (13.6 and 17.8 us for the first two); so are eight for 512 units (28.2 us
-// either way in bf16, 62 -> 68 in float32) and for units of less than 32 KB of keys
-// (7.2 -> 7.6 us at 128 entries of 128 bytes).
+// chain of loads, and eight waves shorten it.  us a step with four -> with eight:
+//   units                          8            64           256          320          512
+//   bf16 d=128 G=4, 512 entries    13.6 -> 12.0 13.9 -> 12.3 17.4 -> 16.1 23.2 -> 23.3 27.6 -> 27.6
+//   the same, 2048                 41.8 -> 36.9 44.1 -> 38.8 56.4 -> 53.5 68.4 -> 69.6 86.3 -> 83.5
+//   bf16 d=128 G=1, 512            10.6 -> 10.5 11.1 -> 11.0 15.7 -> 15.5 20.9 -> 22.4 25.9 -> 26.4
+//   float32 d=128 G=4, 512         33.6 -> 22.0 36.6 -> 24.4 41.8 -> 30.8 46.6 -> 39.4 54.9 -> 49.6
+//   float32 d=64 G=1, 512           9.6 -> 8.4  11.7 -> 9.7  17.0 -> 15.7 20.1 -> 20.8 26.1 -> 26.6
+// Past 256 units the two are within 7% of each other either way, but for float32
+// d=128 and for 4000 bf16 entries (196 -> 178 us, 320 units).  Units of less than 32 KB
+// of keys are short either way: float32 d=64 G=1 5.2 -> 5.8 us at 100 entries and 6.0
+// -> 6.0 at 128, bf16 d=128 G=4 7.6 -> 7.2 at 128.
 constexpr int kWideUnits = 256;
 constexpr size_t kWideKeyBytes = 32 << 10;
 

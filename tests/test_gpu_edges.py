@@ -78,6 +78,65 @@ def test_decode_units_at_the_wide_limit(b):
     _parity(wl, 4)
 
 
+def _full_caches(b, group, d, dtype, n, seed, rule="ave"):
+    """A layer of b units with n entries each (kv_max = n) right after its prompt, and
+    one step's rows: (PDAttention, q, k, v, o)."""
+    from paper_2412_05693_amd.batchmax import PDAttention
+
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(seed)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda", dtype=dt)
+
+    att = PDAttention(b=b, s=n + 50, kv_max=n, block=64, max_gen=8, n_heads=group, n_kv_heads=1,
+                      head_dim=d, dtype=dtype)
+    att.set_rank_rule(rule)
+    att.k[:, :, :n], att.v[:, :, :n] = normal(b, 1, n, d), normal(b, 1, n, d)
+    att.pos[:, :, :n] = torch.arange(n, device="cuda", dtype=torch.int32)
+    att.score[:, :, :n] = torch.rand((b, 1, n), generator=g, device="cuda")
+    att.len.fill_(n)
+    att.resume(n, n + 50)
+    return att, normal(b, group, 1, d), normal(b, 1, 1, d), normal(b, 1, 1, d), normal(b, group, 1, d)
+
+
+@pytest.mark.parametrize("dtype,d,group,n", [
+    # the kernel of more than 256 units over whole and started batches of its loads:
+    # float32 keys 64 (d = 128) or 128 (d = 64) at a time, entries with the step's own
+    ("f32", 128, 4, 63), ("f32", 128, 1, 64), ("f32", 128, 2, 128), ("f32", 64, 4, 127),
+    ("f32", 64, 2, 128), ("f32", 64, 1, 333),
+    # scores and positions past the 1024 that are read ahead
+    ("f32", 128, 2, 1100), ("bf16", 128, 4, 1023), ("bf16", 64, 4, 1024), ("bf16", 128, 1, 2500),
+    ("bf16", 128, 4, 512), ("bf16", 64, 2, 300),
+    # less than 32 KB of keys per unit
+    ("bf16", 128, 4, 100), ("f32", 64, 2, 100),
+], ids=lambda x: str(x))
+def test_decode_does_not_depend_on_the_batch(dtype, d, group, n):
+    # a sample's step gives the same bits in a batch of 257 units as in one of three
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[edges] batch {dtype} d={d} G={group} n={n}", flush=True)
+    b, rows = 257, [0, 131, 256]
+    att, *io = _full_caches(b, group, d, dtype, n, seed=n)
+    sub, *_ = _full_caches(len(rows), group, d, dtype, n, seed=0)
+    for name in ("k", "v", "pos", "score"):
+        getattr(sub, name).copy_(getattr(att, name)[rows])
+    sio = [x[rows].contiguous() for x in io]
+    for t in range(2):
+        att.decode_step(n + 50 + t, *io)
+        sub.decode_step(n + 50 + t, *sio)
+    torch.cuda.synchronize()
+    for i, name in enumerate(("q", "k", "v", "o")):
+        assert torch.equal(io[i][rows], sio[i]), name
+    for name in ("pos", "score", "k", "v", "len"):
+        x, y = getattr(att, name)[rows], getattr(sub, name)
+        if name != "len":
+            x, y = x[:, :, :n], y[:, :, :n]
+        assert torch.equal(x, y), name
+    att.close()
+    sub.close()
+
+
 @pytest.mark.parametrize("dtype,d,group,b,n", [
     ("bf16", 128, 4, 1, 4608),     # chunks of 512 keys: nine whole ones and the step's key
     ("bf16", 128, 1, 2, 4607),     # nine whole ones with it
