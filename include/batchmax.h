@@ -178,6 +178,7 @@ int bm_resume(const bm_dims* dims, const bm_cache* cache, int32_t len, int32_t n
  *   q, o  point at row t0 of [b, n_heads, seq_ld, head_dim] buffers
  *   k, v  point at row t0 of [b, n_kv_heads, seq_ld, head_dim] buffers
  *   seq_ld >= n_tok: rows between consecutive (sample, head) planes.
+ * o may be q itself (attention in place); it must not overlap k or v.
  * Order: t0 must equal the next expected position, 1 <= n_tok <= block,
  * t0 + n_tok <= s, and the cache must hold at most kv_max entries (evict first). */
 int bm_prefill_block(bm_ctx* ctx, int32_t t0, int32_t n_tok, const void* q, const void* k,

@@ -78,6 +78,14 @@ enum {
  * [1, BM_TIMELINE_MAX_RECORDS]. */
 int bm_prefill_timeline(uint64_t* dst, int32_t n_records);
 
+/* Workgroups per position tile that the prefill attention launch of a block of
+ * n_tok tokens with these buffers would have in the context's present state
+ * (small launches share a tile's score sums among several; the results do not
+ * depend on it).  Host arithmetic alone: no device work, nothing read through
+ * the pointers.  -1 for a null context or n_tok or seq_ld out of range. */
+int32_t bm_prefill_tile_workgroups(const bm_ctx* ctx, int32_t n_tok, const void* q, const void* o,
+                                   int32_t seq_ld);
+
 #ifdef __cplusplus
 }
 #endif

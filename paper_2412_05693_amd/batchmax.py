@@ -100,6 +100,7 @@ def _load() -> ctypes.CDLL:
         "bm_probe_stream_read": (ctypes.c_int, [P, SZ, P, I32, I32, P]),
         "bm_probe_mfma": (ctypes.c_int, [I32, P, I32, P]),
         "bm_prefill_timeline": (ctypes.c_int, [P, I32]),
+        "bm_prefill_tile_workgroups": (I32, [P, I32, P, P, I32]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(lib, name)
@@ -117,7 +118,7 @@ EXPORTED = ("bm_abi_version", "bm_last_error", "bm_cache_slots", "bm_workspace_b
             "bm_set_score_accumulation", "bm_set_left_padding", "bm_set_split_event",
             "bm_decode_step", "bm_ctx_len", "bm_ctx_next_pos", "bm_destroy", "bm_synth_qkv",
             "bm_philox4x32_10", "bm_probe_stream_read", "bm_probe_mfma",
-            "bm_prefill_timeline")
+            "bm_prefill_timeline", "bm_prefill_tile_workgroups")
 
 
 def _check(status: int) -> None:
@@ -257,6 +258,10 @@ def bm_prefill_timeline(n_records: int):
     out = np.zeros((n_records, TIMELINE_FIELDS), dtype=np.uint64)
     _check(_lib.bm_prefill_timeline(out.ctypes.data_as(ctypes.c_void_p), n_records))
     return out
+
+
+def bm_prefill_tile_workgroups(ctx: int, n_tok: int, q: int, o: int, seq_ld: int) -> int:
+    return _lib.bm_prefill_tile_workgroups(ctx, n_tok, q, o, seq_ld)
 
 
 def make_dims(*, b, s, kv_max, block, max_gen, n_heads, n_kv_heads, head_dim, dtype,

@@ -727,6 +727,23 @@ BM_EXPORT int bm_probe_mfma(int32_t iters, float* sink, int32_t blocks, hipStrea
   return ok();
 }
 
+BM_EXPORT int32_t bm_prefill_tile_workgroups(const bm_ctx* ctx, int32_t n_tok, const void* q,
+                                             const void* o, int32_t seq_ld) {
+  if (!ctx || n_tok < 1 || n_tok > ctx->dims.block || seq_ld < n_tok) return -1;
+  bm::PrefillArgs a{};
+  a.q = q;
+  a.o = const_cast<void*>(o);
+  a.seq_ld = seq_ld;
+  a.n_heads = ctx->dims.n_heads;
+  a.n_kv_heads = ctx->dims.n_kv_heads;
+  a.n_tok = n_tok;
+  const int ppw = bm::positions_per_wg(ctx->group);
+  a.npt_used = (n_tok + ppw - 1) / ppw;
+  a.units = ctx->units;
+  a.accumulate = ctx->accumulate ? 1 : 0;
+  return bm::prefill_split(a, ctx->dims.head_dim * ctx->elem_bytes);
+}
+
 BM_EXPORT int bm_prefill_timeline(uint64_t* dst, int32_t n_records) {
   if (!bm::timeline_enabled())
     return fail(BM_ERR_UNSUPPORTED, "this library was built without BM_PREFILL_TIMELINE");

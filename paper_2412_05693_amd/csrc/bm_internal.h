@@ -140,6 +140,8 @@ struct SynthArgs {
 
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int head_dim, int group,
                           hipStream_t stream);
+// workgroups per position tile of that launch
+int prefill_split(const PrefillArgs& a, int row_bytes);
 hipError_t launch_score_reduce(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_select(const EvictArgs& a, hipStream_t stream);
 hipError_t launch_fold_cut(const PrefillArgs& pa, const EvictArgs& a, int pt_positions,

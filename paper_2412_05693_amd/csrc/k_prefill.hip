@@ -1166,8 +1166,16 @@ __global__ void __launch_bounds__(256) score_reduce_kernel(PrefillArgs a, int pt
 // store is as long as the sums.
 constexpr int kComputeUnits = 256;
 constexpr int kMaxSplit = 4;
-int split_of(const PrefillArgs& a) {
+// Outputs that overlap the queries rule it out: the workgroups of a tile read the same
+// query rows, and the first stores outputs while others may not have begun (one
+// workgroup reads its rows before it stores them, so attention in place is right).
+// Timeline builds never split: their records are one workgroup's, both sweeps whole.
+int split_of(const PrefillArgs& a, int row_bytes) {
   if (kTimeline || !a.accumulate) return 1;
+  const int64_t planes = (int64_t)a.units * (a.n_heads / a.n_kv_heads);
+  const uintptr_t span = (uintptr_t)(((planes - 1) * a.seq_ld + a.n_tok) * row_bytes);
+  const uintptr_t q = (uintptr_t)a.q, o = (uintptr_t)a.o;
+  if (q < o + span && o < q + span) return 1;
   return max(1, min(kMaxSplit, kComputeUnits / (a.units * a.npt_used)));
 }
 
@@ -1183,7 +1191,7 @@ hipError_t launch_s(const PrefillArgs& a, hipStream_t stream) {
 
 template <bool BF16, int D, int G>
 hipError_t launch_t(PrefillArgs a, hipStream_t stream) {
-  a.nsplit = split_of(a);
+  a.nsplit = split_of(a, Cfg<BF16, D>::RB);
   return a.nsplit > 1 ? launch_s<BF16, D, G, true>(a, stream) : launch_s<BF16, D, G, false>(a, stream);
 }
 
@@ -1210,6 +1218,8 @@ hipError_t launch_prefill(const PrefillArgs& a, int dtype, int head_dim, int gro
   }
   return hipErrorInvalidValue;
 }
+
+int prefill_split(const PrefillArgs& a, int row_bytes) { return split_of(a, row_bytes); }
 
 bool timeline_enabled() { return kTimeline; }
 

@@ -391,3 +391,37 @@ def test_prefill_timeline_only_in_timeline_build():
                        timeout=300)
     assert r.returncode == 0, r.stderr
     assert r.stdout.split() == [str(bmx.BM_ERR_INVALID_ARG)] * 3
+
+
+def test_prefill_tile_workgroups():
+    """Which launches share a position tile among several workgroups, and that one
+    whose outputs land in its own query rows does not: the others of a tile would
+    read queries that the first has already overwritten."""
+    # 8 heads over 2 KV heads, 128 / 4 positions per workgroup
+    def split(b, n_tok=64, q=FAKE, o=FAKE + (1 << 36), accumulate=True, **kw):
+        d = dims(b=b, s=4096, **kw)
+        ctx = _ctx(d, 128, 192)
+        if not accumulate:
+            bmx.bm_set_score_accumulation(ctx, 0)
+        n = bmx.bm_prefill_tile_workgroups(ctx, n_tok, q, o, 4096)
+        bmx.bm_destroy(ctx)
+        return n
+
+    # workgroups = b x 2 KV heads x 2 tiles
+    assert [split(b) for b in (1, 16, 17, 21, 22, 32, 33, 64, 65)] == [4, 4, 3, 3, 2, 2, 1, 1, 1]
+    assert split(1, accumulate=False) == 1
+    assert split(64, n_tok=1) == 2 and split(64, n_tok=33) == 1
+    # in place, and every other overlap of the rows the launch touches:
+    # (b x 8 heads - 1) planes of 4096 rows, and n_tok rows, of 256 or 512 bytes
+    for kw, row in ((dict(dtype="bf16"), 256), (dict(dtype="f32"), 512)):
+        span = (7 * 4096 + 64) * row
+        assert split(1, o=FAKE, **kw) == 1
+        assert split(1, o=FAKE + span - 16, **kw) == 1
+        assert split(1, q=FAKE + span - 16, o=FAKE, **kw) == 1
+        assert split(1, o=FAKE + span, **kw) == 4
+        assert split(1, q=FAKE + span, o=FAKE, **kw) == 4
+    assert bmx.bm_prefill_tile_workgroups(0, 1, FAKE, FAKE, 1) == -1
+    ctx = _ctx(dims(), 0, 0)
+    for n_tok, ld in ((0, 64), (65, 65), (64, 63)):
+        assert bmx.bm_prefill_tile_workgroups(ctx, n_tok, FAKE, FAKE, ld) == -1
+    bmx.bm_destroy(ctx)

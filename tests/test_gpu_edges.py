@@ -192,6 +192,35 @@ def test_long_decode_chunks(dtype, d, group, b, n):
     att.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_attention_in_place(dtype):
+    # outputs written over the queries (and elsewhere in one buffer) are those of
+    # separate buffers, and so are the scores and the kept entries
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from pd_harness import make_pd
+
+    wl = C2.with_(name="inplace", hh_mode="scatter", n_sinks=4, b=2, n_heads=4, n_kv_heads=2, dtype=dtype,
+                  head_dim=64, s=400, kv_max=130, block=100, n_decode=3)
+    print(f"[edges] in place {dtype}", flush=True)
+    q, k, v = synth.batch_inputs(wl, "cuda")
+    ref = torch.zeros_like(q)
+    both = torch.cat([q, torch.zeros_like(q)])
+    one = q.clone()
+    results = []
+    for qq, oo in ((q, ref), (one, one), (both[:2], both[2:])):
+        pd = make_pd(wl)
+        pd.run_prefill(qq, k, v, oo)
+        pd.run_decode(qq, k, v, oo)
+        torch.cuda.synchronize()
+        n = pd.length
+        results.append((oo.clone(), pd.score[..., :n].clone(), pd.pos[..., :n].clone()))
+        pd.close()
+    for got in results[1:]:
+        for x, y in zip(got, results[0]):
+            assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("what", ["shape", "dtype", "stride", "device", "rows", "row"])
 def test_calls_that_are_refused(what):
     if not torch.cuda.is_available():
