@@ -592,6 +592,12 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
         for (int r = 0; r < 16; ++r) oacc[mt][r] *= alpha;
     }
   };
+  // What the logits are taken against.  With left padding a row's first tiles can be
+  // all pad keys: m_run is still -inf there and every logit is -inf, so subtract 0 to
+  // get p = 0, not NaN.  A launch with padding keeps to that after its pads are gone
+  // (logits that overflow to -inf weigh nothing there); without padding every row
+  // sees a key in its first tile.
+  auto reference = [&]() BM_LAMBDA { return PAD && m_run == kNegInf ? 0.0f : m_run; };
   auto exp_tile = [&](float m_sub) BM_LAMBDA {
     float psum = 0.0f;
 #pragma unroll
@@ -629,10 +635,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sacc[st][r]);
     raise_max(xhalf_max(tmax));
-    // with left padding a row's first tiles can be all pad keys: m_run is still
-    // -inf there and every logit is -inf, so subtract 0 to get p = 0, not NaN
-    // (without padding every row sees a key in its first tile)
-    exp_tile(PAD && m_run == kNegInf ? 0.0f : m_run);
+    exp_tile(reference());
   };
 
   // A operand (V^T) of the PV MFMA: lane (n, h) needs V[key][32 mt + n] for the
@@ -719,9 +722,10 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
         vf[j % NB] = u32x4{l2.x, l2.y, h2.x, h2.y};
       };
       float x[2][2], e[2][2], psum = 0.0f;
+      const float m_sub = reference();
       auto args = [&](int p) BM_LAMBDA {   // pair p: logits 2 p, 2 p + 1 of the lane
 #pragma unroll
-        for (int l = 0; l < 2; ++l) x[p & 1][l] = fmaf(zo[p / 8][2 * (p % 8) + l], c2, -m_run);
+        for (int l = 0; l < 2; ++l) x[p & 1][l] = fmaf(zo[p / 8][2 * (p % 8) + l], c2, -m_sub);
       };
       auto exps = [&](int p) BM_LAMBDA {
 #pragma unroll
@@ -872,7 +876,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
           ++t1;
         }
         // the run's last tile: P (its PV product belongs to the next step)
-        exp_tile(m_run);
+        exp_tile(reference());
         p_live = true;
       }
     }

@@ -192,6 +192,55 @@ def test_long_decode_chunks(dtype, d, group, b, n):
     att.close()
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128)])
+def test_padded_launch_with_logits_of_minus_infinity(dtype, d):
+    # a launch with left padding whose units hold no pad any more: the first key tiles
+    # give every query a logit of -inf (the products overflow), so a row's maximum is
+    # -inf until its first ordinary key; such keys weigh nothing
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2412_05693_amd.batchmax import PDAttention
+
+    print(f"[edges] -inf logits {dtype} d={d}", flush=True)
+    b, G, n, t0, block = 2, 2, 320, 400, 64
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(d)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda", dtype=dt)
+
+    att = PDAttention(b=b, s=t0 + block, kv_max=n, block=block, max_gen=0, n_heads=G, n_kv_heads=1,
+                      head_dim=d, dtype=dtype)
+    kc, vc, k, v, q = (normal(b, h, r, d) for h, r in ((1, n), (1, n), (1, block), (1, block), (G, block)))
+    q[..., 0], kc[..., 0], k[..., 0] = 1e30, 0, 0
+    kc[:, :, :192, 0] = -1e30
+    att.k[:, :, :n], att.v[:, :, :n] = kc, vc
+    att.pos[:, :, :n] = torch.arange(60, 60 + n, device="cuda", dtype=torch.int32)
+    att.score.zero_()
+    att.len.fill_(n)
+    att.set_left_padding(torch.tensor([0, 50], dtype=torch.int32, device="cuda"))
+    att.resume(n, t0)
+    o = torch.empty_like(q)
+    att.prefill_block(t0, block, q, k, v, o, row=0)
+    kk, vv = torch.cat([kc, k], dim=2).double(), torch.cat([vc, v], dim=2).double()
+    ref, score = torch.zeros_like(o, dtype=torch.float64), torch.zeros((b, n + block), device="cuda").double()
+    hidden = torch.ones((block, block), device="cuda").triu(1).bool()
+    for i in range(b):
+        for h in range(G):
+            z = (q[i, h].double() @ kk[i, 0].T) / math.sqrt(d)      # -1e60: a weight of 0
+            z[:, n:].masked_fill_(hidden, float("-inf"))
+            p = torch.softmax(z, dim=-1)
+            ref[i, h] = p @ vv[i, 0]
+            score[i] += p.sum(0)
+    err = (o.double() - ref).abs().max().item()
+    # the outputs' rounding to bf16 (2^-9 of values up to 4) and the weights'; float32 sums
+    assert err <= (2e-2 if dtype == "bf16" else 1e-4), err
+    got = att.score[:, 0, :n + block].double()
+    assert bool((got[:, :192] == 0).all())
+    assert ((got - score).abs() / (score + 1e-3)).max().item() < 1e-3
+    att.close()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_attention_in_place(dtype):
     # outputs written over the queries (and elsewhere in one buffer) are those of
