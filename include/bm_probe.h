@@ -18,6 +18,8 @@
 #include <stdint.h>
 #include <hip/hip_runtime_api.h>
 
+#include "batchmax.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif

@@ -53,7 +53,7 @@ typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 // the LDS object at byte `off` (an address kept as a number, so that it takes
 // one register and an immediate offset)
 template <typename T>
-__device__ __forceinline__ T* lds_at(uint32_t off) { return (T*)off; }
+__device__ __forceinline__ T* lds_at(uint32_t off) { return (T*)(uintptr_t)off; }
 
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr float kPosInf = __builtin_huge_valf();
@@ -285,20 +285,28 @@ __device__ __forceinline__ int copy_offset(const Geo& s, int j) {
 // so that the compiler does not order the tile reads behind the copies in flight
 // (it cannot tell the buffers apart once their choice is a run-time value):
 // tile_fence() waits for a wave's copies, and the barrier behind it for everyone's.
+// A load may read its resource five wait states after a vector instruction wrote one
+// of those scalar registers (a reload of a spilled one is such an instruction), and the
+// compiler does not count the states inside a block: s_mov and s_nop 3 are all five.
+// M0 is a reserved register, so the compiler warns that it does not save it for a
+// block that names it; no other code of these kernels uses M0 (checked on the built
+// library by a test), and the warning is off for the three blocks alone.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int NCOPY>
 __device__ __forceinline__ void copy_tile(uint32_t dst, u32x4 rsrc, const int (&off)[NCOPY], int w) {
   static_assert(NCOPY % 4 == 0 || NCOPY == 2, "copies per wave and tile");
   const uint32_t lds = __builtin_amdgcn_readfirstlane(dst + w * (NCOPY * 1024));
   if constexpr (NCOPY == 2) {
     asm volatile(
-        "s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds\n\t"
+        "s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds\n\t"
         "buffer_load_dwordx4 %1, %2, 0 offen offset:1024 lds"
         ::"v"(off[0]), "v"(off[1]), "s"(rsrc), "s"(lds) : "m0");
   } else {
 #pragma unroll
     for (int j = 0; j < NCOPY; j += 4)
       asm volatile(
-          "s_mov_b32 m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
+          "s_mov_b32 m0, %5\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
           "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
           "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
           "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
@@ -306,6 +314,13 @@ __device__ __forceinline__ void copy_tile(uint32_t dst, u32x4 rsrc, const int (&
           "s"(__builtin_amdgcn_readfirstlane(lds + 1024 * j)) : "m0");
   }
 }
+
+// 64 words, one from byte offset `off` of each lane, to LDS at `dst`
+__device__ __forceinline__ void copy_words(uint32_t dst, u32x4 rsrc, int off) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dword %0, %1, 0 offen lds"
+               ::"v"(off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(dst)) : "m0");
+}
+#pragma clang diagnostic pop
 
 // wait for the wave's copies; LDS may hold new tiles from here on
 __device__ __forceinline__ void tile_fence() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -451,10 +466,7 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     if (PAD && s.pad > 0 && ti.cache && s.w == 0) {
       // the tile's key positions, in key order, next to the K rows
       const u32x4 r = rsrc_of(pos_base, a.len0 * 4);
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
-                   ::"v"((ti.base + s.lane) * 4), "s"(r),
-                   "s"(__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)pk_ring[t % 3]))
-                   : "m0");
+      copy_words((uint32_t)(uintptr_t)(lds_void*)pk_ring[t % 3], r, (ti.base + s.lane) * 4);
     }
   };
   // bit k set: key k of tile ti is a pad token (cache keys through the LDS copy
