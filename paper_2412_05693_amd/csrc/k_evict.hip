@@ -22,6 +22,8 @@
 namespace bm {
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
 constexpr int kMaxPer = kMaxCap / 256;  // keys per thread held in registers
 
 // exclusive prefix count of `flag` over the workgroup in thread order; returns
@@ -418,11 +420,12 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
   char* kc = static_cast<char*>(a.kc) + (int64_t)u * a.cap * row_bytes;
   char* vc = static_cast<char*>(a.vc) + (int64_t)u * a.cap * row_bytes;
   // four loads in flight per thread: a chunk's store would otherwise wait for its
-  // load before the next load goes out (sources and holes share no slot)
+  // load before the next load goes out (sources and holes share no slot).  (An array
+  // of HIP's uint4, a structure, would be kept in scratch memory.)
   constexpr int UM = 4;
   const int chunks = m * 2 * cpr;
   for (int c0 = tid; c0 < chunks; c0 += 256 * UM) {
-    uint4 x[UM];
+    u32x4 x[UM];
     char* to[UM];
 #pragma unroll
     for (int i = 0; i < UM; ++i) {
@@ -431,12 +434,12 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
       const int rem = c - mv * 2 * cpr;
       const int which = rem / cpr, cc = rem - which * cpr;
       char* base = (which ? vc : kc) + cc * 16;
-      x[i] = *reinterpret_cast<const uint4*>(base + (int64_t)srcs[mv] * row_bytes);
+      x[i] = *reinterpret_cast<const u32x4*>(base + (int64_t)srcs[mv] * row_bytes);
       to[i] = base + (int64_t)holes[mv] * row_bytes;
     }
 #pragma unroll
     for (int i = 0; i < UM; ++i)
-      if (c0 + 256 * i < chunks) *reinterpret_cast<uint4*>(to[i]) = x[i];
+      if (c0 + 256 * i < chunks) *reinterpret_cast<u32x4*>(to[i]) = x[i];
   }
   for (int mv = tid; mv < m; mv += 256) {
     const int sj = srcs[mv], dj = holes[mv];

@@ -62,3 +62,9 @@ def test_copies_into_lds_wait_for_their_scalar_registers(kernels):
             if re.search(r"\bm0\b", ins):
                 assert ins.startswith("s_mov_b32 m0,") and code[i + 2].endswith(" lds"), (name, ins)
     assert blocks > 1000
+
+
+def test_no_kernel_uses_scratch_memory(kernels):
+    """Registers and LDS hold every value: no kernel spills to (or indexes) scratch."""
+    used = {n for n, code in kernels.items() for ins in code if ins.startswith("scratch_")}
+    assert not used, sorted(used)
