@@ -40,10 +40,86 @@ def _parity(wl, units, **kw):
     (256, 31),     # a block shorter than a wave's rows
 ], ids=lambda x: str(x))
 def test_prefill_runs_of_tiles(d, kv_heads, kv, block):
-    # runs of 0 to 5 unmasked tiles with every kind of tile behind them, in both sweeps
+    # runs of 0 to 4 unmasked tiles in sweep 1 with every kind of tile behind them; the
+    # launches are small, so four workgroups share sweep 2, at most 3 unmasked tiles each
+    # (longer runs and one workgroup per tile: the next two tests)
     wl = C2.with_(name="edges", hh_mode="scatter", n_sinks=4, b=1, n_heads=4, n_kv_heads=kv_heads,
                   head_dim=d, s=kv + 3 * block + 1, kv_max=kv, block=block, n_decode=0)
     _parity(wl, wl.units, rule="tova" if kv == 192 else "ave")
+
+
+def _prompts(b, group, d, dtype, s, padded, seed):
+    """Inputs of b samples with one KV head: (q, k, v, pads)."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v = (torch.randn((b, h, s, d), generator=g, device="cuda", dtype=dt) for h in (group, 1, 1))
+    k *= torch.exp(0.5 * torch.randn((b, 1, s, 1), generator=g, device="cuda")).to(dt)
+    pads = None
+    if padded:
+        # none, some that the first cuts remove, and more than a block
+        pads = torch.tensor([(0, 37, s // 2)[i % 3] for i in range(b)], device="cuda", dtype=torch.int32)
+    return q, k, v, pads
+
+
+def _prefilled(x, rows, kv, block, rule):
+    """The prompt of the samples `rows` through one layer: {name: tensor} of what it
+    leaves, and the workgroups per position tile of a whole block over a full cache."""
+    from paper_2412_05693_amd import batchmax as bmx
+
+    q, k, v, pads = (None if t is None else t[rows].contiguous() for t in x)
+    o = torch.empty_like(q)
+    b, group, s, d = q.shape
+    att = bmx.PDAttention(b=b, s=s, kv_max=kv, block=block, max_gen=0, n_heads=group, n_kv_heads=1,
+                          head_dim=d, dtype="bf16" if q.dtype == torch.bfloat16 else "f32")
+    att.set_rank_rule(rule)
+    if pads is not None:
+        att.set_left_padding(pads)
+    nsplit = bmx.bm_prefill_tile_workgroups(att.ctx, block, q.data_ptr(), o.data_ptr(), s)
+    att.run_prefill(q, k, v, o, fused_cut=True)
+    torch.cuda.synchronize()
+    n = att.length
+    out = {"o": o, "len": att.len.clone(),
+           **{name: getattr(att, name)[:, :, :n].clone() for name in ("score", "pos", "k", "v")}}
+    att.close()
+    return out, nsplit
+
+
+@pytest.mark.parametrize("padded", [False, True], ids=["", "padded"])
+@pytest.mark.parametrize("kv,block,rule", [
+    (200, 65, "ave"),      # a partial cache tile; a block of one tile and one row
+    (512, 256, "tova"),    # runs of eight tiles and more; whole tiles
+    (330, 129, "tova"),
+], ids=lambda x: str(x))
+@pytest.mark.parametrize("dtype,d,group", [(t, d, g) for t in ("bf16", "f32") for d in (64, 128) for g in (1, 2, 4)])
+def test_prefill_does_not_depend_on_the_workgroups_per_tile(dtype, d, group, kv, block, rule, padded):
+    # small launches share a position tile's sums among up to four workgroups: a
+    # sample's outputs, scores, kept entries and rows (under tova, cut by the last
+    # query's weights) are the same bits in launches of four, three, two and one
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[edges] tile workgroups {dtype} d={d} G={group} kv={kv} B={block} {rule} padded={padded}", flush=True)
+    npt = -(-block // (128 // group))
+    sizes = {3: 85 // npt, 2: 128 // npt, 1: 128 // npt + 1}
+    x = _prompts(sizes[1], group, d, dtype, kv + 3 * block + 1, padded, seed=kv)
+    rows = [0, 1, sizes[3] - 1]
+    ref, nsplit = _prefilled(x, rows, kv, block, rule)
+    assert nsplit == 4
+    for want, b in sizes.items():
+        got, nsplit = _prefilled(x, list(range(b)), kv, block, rule)
+        assert nsplit == want
+        for name in ref:
+            assert torch.equal(got[name][rows], ref[name]), (want, name)
+
+
+@pytest.mark.parametrize("kv,block", [(200, 65), (512, 256)], ids=lambda x: str(x))
+@pytest.mark.parametrize("dtype,d,kv_heads", [(t, d, h) for t in ("bf16", "f32") for d in (64, 128) for h in (1, 2, 4)])
+def test_prefill_of_large_launches(dtype, d, kv_heads, kv, block):
+    # more workgroups than are ever split, checked on a few units
+    npt = -(-block // (128 * kv_heads // 4))
+    wl = C2.with_(name="edges", hh_mode="scatter", n_sinks=4, b=-(-129 // (npt * kv_heads)), n_heads=4,
+                  n_kv_heads=kv_heads, head_dim=d, dtype=dtype, s=kv + 2 * block + 1, kv_max=kv, block=block,
+                  n_decode=0, pad_max=90 if kv == 200 else 0)
+    _parity(wl, 3)
 
 
 @pytest.mark.parametrize("case", [
