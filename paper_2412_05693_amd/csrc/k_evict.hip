@@ -416,30 +416,31 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
   // 3. the moves: the i-th source into the i-th hole (disjoint slot ranges)
   const int m = min(hbase, sbase);
   const int row_bytes = a.head_dim * a.elem_bytes;
-  const int cpr = row_bytes / 16;
+  const int lg = 31 - __clz(row_bytes / 16);   // 8, 16 or 32 chunks of 16 bytes per row
   char* kc = static_cast<char*>(a.kc) + (int64_t)u * a.cap * row_bytes;
   char* vc = static_cast<char*>(a.vc) + (int64_t)u * a.cap * row_bytes;
   // four loads in flight per thread: a chunk's store would otherwise wait for its
-  // load before the next load goes out (sources and holes share no slot).  (An array
-  // of HIP's uint4, a structure, would be kept in scratch memory.)
+  // load before the next load goes out (sources and holes share no slot).  A cut of
+  // few moves has one chunk per thread: rounds past the last chunk are skipped (the
+  // same for every thread) and addresses are formed with shifts.  (An array of HIP's
+  // uint4, a structure, would be kept in scratch memory.)
   constexpr int UM = 4;
-  const int chunks = m * 2 * cpr;
-  for (int c0 = tid; c0 < chunks; c0 += 256 * UM) {
+  const int chunks = m << (lg + 1);
+  for (int b0 = 0; b0 < chunks; b0 += 256 * UM) {
     u32x4 x[UM];
     char* to[UM];
 #pragma unroll
     for (int i = 0; i < UM; ++i) {
-      const int c = min(c0 + 256 * i, chunks - 1);
-      const int mv = c / (2 * cpr);
-      const int rem = c - mv * 2 * cpr;
-      const int which = rem / cpr, cc = rem - which * cpr;
-      char* base = (which ? vc : kc) + cc * 16;
+      if (b0 + 256 * i >= chunks) break;
+      const int c = min(b0 + 256 * i + tid, chunks - 1);
+      const int mv = c >> (lg + 1);
+      char* base = ((c >> lg) & 1 ? vc : kc) + (c & ((1 << lg) - 1)) * 16;
       x[i] = *reinterpret_cast<const u32x4*>(base + (int64_t)srcs[mv] * row_bytes);
       to[i] = base + (int64_t)holes[mv] * row_bytes;
     }
 #pragma unroll
     for (int i = 0; i < UM; ++i)
-      if (c0 + 256 * i < chunks) *reinterpret_cast<u32x4*>(to[i]) = x[i];
+      if (b0 + 256 * i + tid < chunks) *reinterpret_cast<u32x4*>(to[i]) = x[i];
   }
   for (int mv = tid; mv < m; mv += 256) {
     const int sj = srcs[mv], dj = holes[mv];
