@@ -425,13 +425,31 @@ int check_rule(const bm_ctx* ctx) {
   return BM_OK;
 }
 
-// Cuts of up to this many bytes of moved rows per unit go through one launch, whose
-// one workgroup per unit also moves the rows; more rows are moved by a launch of
-// their own with many workgroups per unit.  40 units of 433 entries, up to 100 rows of
-// 256 bytes: 5.2 + 4.5 us in two launches; s=1999 in blocks of 100 with such cuts
-// 484 -> 464 us.  One workgroup moves 16 KB per round of its loads, so the limit is
-// four rounds, about as long as the launch that is saved.
+// Whether a cut goes through one launch, whose one workgroup per unit also moves the
+// rows; otherwise a launch of its own moves them with many workgroups per unit.  One
+// workgroup moves 16 KB per round of its loads, so the limit is four rounds, about as
+// long as the launch that is saved.  Ranking more than 2048 entries takes one workgroup
+// longer too, so units that leave compute units idle get two rounds there.  us in two
+// launches -> in one, by units:
+//   entries, KB moved  8            40           256          512          2048
+//   433, 25            7.0 -> 5.7   7.7 -> 6.1   9.8 -> 7.1   12.5 -> 8.9  26.7 -> 17.8
+//   640, 64            8.6 -> 8.0   9.0 -> 8.3   12.6 -> 10.2 17.6 -> 13.9 57.2 -> 47.8
+//   2048, 64           11.9 -> 11.6 12.4 -> 12.0 17.0 -> 15.7 22.7 -> 19.5 78.9 -> 73.1
+//   3136, 32           13.1 -> 12.2 13.6 -> 12.8 17.3 -> 16.0 22.1 -> 19.8 66.0 -> 59.8
+//   3200, 64           13.2 -> 14.1 13.9 -> 15.0 19.5 -> 18.8 26.3 -> 23.1 93.0 -> 90.6
+//   4096, 32 (d=128)   13.2 -> 12.5 14.2 -> 13.8 19.3 -> 18.2 24.2 -> 21.3 73.4 -> 72.7
+//   4096, 32 (d=64)    13.4 -> 13.6 14.0 -> 14.0 19.3 -> 18.5 24.2 -> 21.9 75.5 -> 72.3
+//   4096, 64           13.6 -> 15.2 14.7 -> 15.7 21.2 -> 20.5 27.8 -> 24.6 100 -> 96
+// 8192 units of 640 entries, 64 KB: 221 -> 198.
 constexpr int64_t kOneLaunchMoveBytes = 64 << 10;
+constexpr int kOneLaunchEntries = 2048;
+constexpr int kOneLaunchUnits = 256;      // a workgroup for every compute unit
+
+bool one_launch_cut(const bm::EvictArgs& a, int max_moves) {
+  const int64_t bytes = (int64_t)max_moves * 2 * a.head_dim * a.elem_bytes;
+  const bool idle = a.n > kOneLaunchEntries && a.units < kOneLaunchUnits;
+  return a.n <= bm::kMaxCap && bytes <= (idle ? kOneLaunchMoveBytes / 2 : kOneLaunchMoveBytes);
+}
 
 // Enqueue the cut of every unit from ctx->len down to `target` entries (select
 // + compaction), ranked at curr_id.  Requires ctx->len > target; the caller has
@@ -458,8 +476,7 @@ int cut_to(bm_ctx* ctx, int target, int32_t curr_id, hipStream_t stream) {
   const int n_evict = ctx->len - target;
   const int max_moves = n_evict < target ? n_evict : target;
   hipError_t e;
-  if (a.n <= bm::kMaxCap &&
-      (int64_t)max_moves * 2 * a.head_dim * a.elem_bytes <= kOneLaunchMoveBytes) {
+  if (one_launch_cut(a, max_moves)) {
     e = bm::launch_cut(a, stream);
     if (e != hipSuccess) return hip_fail(e, "cut launch");
     ctx->len = target;

@@ -292,13 +292,21 @@ __global__ void __launch_bounds__(256) compact_kernel(EvictArgs a, int nchunks) 
   }
 }
 
+// rows that a cut of one unit moves at most
+__host__ __device__ __forceinline__ int most_moves(const EvictArgs& a) {
+  return a.n - a.kv_max < a.kv_max ? a.n - a.kv_max : a.kv_max;
+}
+
 // K7: the fold of K1's partial column sums, the cut and the compaction of one
 // unit in one workgroup (the block's Algorithm 1 step in one launch instead of
 // three).  The folded scores, the positions and TOVA's weights stay in LDS, the
 // keys in registers; the hole and source lists are built in LDS; the moves copy
 // K and V rows with 16-byte loads and stores.  Needs n <= kMaxCap.
 // KP: keys per thread held in registers (n <= 256 KP).  FOLD: off for a cut by
-// itself, whose scores are complete
+// itself, whose scores are complete.  That one keeps the two lists alone in LDS and
+// reads the moved entries' scores, positions and weights again: arrays of all n
+// entries (82 KB at 4096) left a compute unit one workgroup, and the launch took
+// twice the time of select and compaction (4096 entries to 4064, 2048 units: 107 us).
 template <int KP, bool FOLD>
 __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs a,
                                                         int pt_positions) {
@@ -307,15 +315,17 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
   __shared__ int s_need;
   __shared__ uint32_t s_cnt[4 * kMaxPer];
   __shared__ int s_tot[2];
-  // per-slot LDS arrays, n4 = n rounded up to 4 entries each (dynamic size)
+  // dynamic LDS: per-slot arrays of n4 entries each (n rounded up to 4) with FOLD, then
+  // the two lists (launch_cut_t gives the size)
   extern __shared__ __attribute__((aligned(16))) char k7_lds[];
   const int n = a.n;
   const int n4 = (n + 3) & ~3;
+  const int list_len = FOLD ? n4 : most_moves(a);
   float* sc = reinterpret_cast<float*>(k7_lds);
   int32_t* ps = reinterpret_cast<int32_t*>(sc + n4);
   float* lw = reinterpret_cast<float*>(ps + n4);
-  int32_t* holes = reinterpret_cast<int32_t*>(lw + n4);
-  int32_t* srcs = holes + n4;
+  int32_t* holes = reinterpret_cast<int32_t*>(k7_lds) + (FOLD ? 3 * n4 : 0);
+  int32_t* srcs = holes + list_len;
   const int u = blockIdx.x;
   const int tid = threadIdx.x;
   const int per = (n + 255) / 256;
@@ -388,10 +398,12 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
       const int i = i0 + f, j = tid + 256 * i;
       key[i] = ~0ull;
       if (i < per && j < n) {
-        if constexpr (FOLD) score[j] = acc[f];
-        sc[j] = acc[f];
-        ps[j] = p[f];
-        lw[j] = l[f];
+        if constexpr (FOLD) {
+          score[j] = acc[f];
+          sc[j] = acc[f];
+          ps[j] = p[f];
+          lw[j] = l[f];
+        }
         key[i] = rank_key(a.rule, acc[f], l[f], p[f], a.curr_id);
       }
     }
@@ -409,12 +421,15 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
   const uint64_t thr = radix_kth(key_of, KP, per, n, n - a.kv_max, position_bits(a.curr_id), hist,
                                  &s_prefix, &s_need);
   build_lists([&](int i) { return key[i] <= thr; }, KP, per, n, a.kv_max, s_cnt, s_tot,
-              [&](bool hole, int idx, int j) { (hole ? holes : srcs)[idx] = j; });
+              [&](bool hole, int idx, int j) {
+                // (entries of one position twice, which no schedule makes, could list more)
+                if (FOLD || idx < list_len) (hole ? holes : srcs)[idx] = j;
+              });
   const int hbase = s_tot[0], sbase = s_tot[1];
   __syncthreads();
 
   // 3. the moves: the i-th source into the i-th hole (disjoint slot ranges)
-  const int m = min(hbase, sbase);
+  const int m = min(min(hbase, sbase), list_len);
   const int row_bytes = a.head_dim * a.elem_bytes;
   const int lg = 31 - __clz(row_bytes / 16);   // 8, 16 or 32 chunks of 16 bytes per row
   char* kc = static_cast<char*>(a.kc) + (int64_t)u * a.cap * row_bytes;
@@ -444,9 +459,9 @@ __global__ void __launch_bounds__(256) fold_cut_kernel(PrefillArgs pa, EvictArgs
   }
   for (int mv = tid; mv < m; mv += 256) {
     const int sj = srcs[mv], dj = holes[mv];
-    score[dj] = sc[sj];
-    pos[dj] = ps[sj];
-    if (last) last[dj] = lw[sj];
+    score[dj] = FOLD ? sc[sj] : score[sj];
+    pos[dj] = FOLD ? ps[sj] : pos[sj];
+    if (last) last[dj] = FOLD ? lw[sj] : last[sj];
   }
   if (tid == 0) a.len[u] = a.kv_max;
 }
@@ -458,7 +473,7 @@ namespace {
 template <bool FOLD>
 hipError_t launch_cut_t(const PrefillArgs& pa, const EvictArgs& a, int pt_positions, hipStream_t stream) {
   if (a.n > kMaxCap) return hipErrorInvalidValue;
-  const size_t lds = 5 * sizeof(int32_t) * (size_t)((a.n + 3) & ~3);
+  const size_t lds = sizeof(int32_t) * (FOLD ? 5 * (size_t)((a.n + 3) & ~3) : 2 * (size_t)most_moves(a));
   const dim3 grid((unsigned)a.units);
   if (a.n <= 256 * 3)
     hipLaunchKernelGGL((fold_cut_kernel<3, FOLD>), grid, dim3(256), lds, stream, pa, a, pt_positions);

@@ -143,6 +143,20 @@ def test_cut_on_crafted_state(n, e, patterns):
     _run_cut(n, e, "sum", unit, patterns)
 
 
+@pytest.mark.parametrize("n,e", [
+    (2048, 128), (2048, 129),                         # 64 KB of moves: one launch, and two
+    (2049, 64), (2049, 65),                           # 32 KB past 2048 entries
+    (4096, 64), (4096, 65), (4096, 2), (70, 69),      # the most entries; few; one kept
+], ids=lambda x: str(x))
+def test_cut_at_the_edges_of_one_launch(n, e):
+    patterns = ("uniform", "ties", "spread", "byte2")
+
+    def unit(rng, i):
+        return _positions(rng, n), _scores(patterns[i], n, e, rng)
+
+    _run_cut(n, e, "sum", unit, patterns)
+
+
 AVE_PATTERNS = ("equal", "ties", "dyadic", "dyadic_small")
 
 
@@ -232,3 +246,39 @@ def test_decode_eviction_exact_ties(kv_max):
             err = np.max(np.abs(g_o[bi, h * G:(h + 1) * G, 0] - ref))
             assert err <= 1e-4, (tag, err)
     pd.close()
+
+
+def _cut_us(units, n, removed):
+    """Median time of the cut of n entries by themselves down to n - removed."""
+    att = PDAttention(b=units, s=n + 100, kv_max=n - removed, block=removed, max_gen=0, n_heads=1,
+                      n_kv_heads=1, head_dim=128, dtype="bf16")
+    att.set_rank_rule("sum")
+    att.k.zero_()
+    att.v.zero_()
+    score = torch.rand(att.score.shape, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    pos = torch.arange(att.cap, device="cuda", dtype=torch.int32).expand(score.shape).contiguous()
+    wait = torch.empty(1 << 28, device="cuda")
+    times = []
+    for _ in range(7):
+        att.score.copy_(score)
+        att.pos.copy_(pos)
+        att.resume(n, n + 100)
+        wait.zero_()                # work ahead of the cut, so that the host is not what is timed
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        att.evict_compact(n + 99)
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3)
+    att.close()
+    return sorted(times)[3]
+
+
+def test_time_of_large_cuts_grows_with_their_entries():
+    # the same moves with twice the entries to rank: the latter is reading twice the
+    # scores, not waiting for a place on a compute unit (2.7 times the time when one
+    # workgroup of the larger cut took a unit's LDS; 1.4 when it does not)
+    _need_gpu()
+    t1, t2 = _cut_us(2048, 2048, 32), _cut_us(2048, 4096, 32)
+    print(f"[select] 2048 units, 32 removed: {t1:.1f} us of 2048 entries, {t2:.1f} us of 4096", flush=True)
+    assert t2 < 2 * t1
