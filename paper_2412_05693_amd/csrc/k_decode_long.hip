@@ -231,7 +231,8 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(LongDecodeArgs a) {
   const float* part = a.part + ((int64_t)u * a.nsplit * G + g) * (D + 2);
   const int64_t stride = (int64_t)G * (D + 2);   // floats between a head's chunks
   const int n = a.nsplit;
-  // chunk weights; thread c holds chunk c (and c + 256, ... of very long caches)
+  // chunk weights; thread c holds chunk c (the longest cache has kMaxSplits)
+  static_assert(kMaxSplits <= 256, "a thread per chunk");
   float m = kNegInf;
   for (int c = tid; c < n; c += 256) m = fmaxf(m, part[c * stride + D]);
   m = lanes::wave_max(m);

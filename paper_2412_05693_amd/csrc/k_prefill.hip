@@ -705,12 +705,12 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
 
   // One step of the interleaved loop: QK^T of tile t (into zn), the softmax of
   // tile t - 1 (zo, whose running maximum is settled) and its PV product.
-  // What bounds it: per tile and wave 1024 cycles of MFMA, ~750 of VALU work and
-  // 500 of LDS reads; two waves per SIMD cover each other's phases only in part
-  // (one wave: 2550 cycles a tile with the phases one after the other, 2200 like
-  // this; two waves: 3700 and 3300 a round), and at full load on real data the
-  // card holds the clock near 2.0 of 2.4 GHz.  So the order is pinned, MFMA by
-  // MFMA: the QK MFMAs with 24 of a lane's 32 logits between them, then the PV
+  // What bounds it: per tile and wave 1024 cycles of MFMA (32 of 32 cycles) beside the
+  // softmax's VALU work and the operands' LDS reads; two waves per SIMD cover each
+  // other's phases only in part (b=64 s=4096, bound 512: counters put the matrix pipe
+  // at 40% of a launch's cycles, 30% with the phases one after the other, and the clock
+  // at 2.0 of 2.4 GHz; a tile of this sweep takes 1.92 us of two workgroups' time, 2.16
+  // before).  So the order is pinned, MFMA by MFMA: the QK MFMAs with 24 of a lane's 32 logits between them, then the PV
   // MFMAs with the last 8 and the maximum of zn.  VALU work is staged over three
   // places (x = logit - reference, e = exp2, sum and pack), so that no
   // instruction waits for the one before it; operand reads go out kAhead MFMAs
@@ -1067,8 +1067,8 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
     wait_and_sync(BM_TL_S2_WAIT, BM_TL_S2_BARRIER);
     if (t > 0) store_sums(t - 1);
   };
-  // one half tile of the interleaved loop: QK^T of key half U of tile t (into
-  // snew) and the sums of the half before it (sold)
+  // the sums of one key half of tile t by themselves (z: its logits): the first half
+  // before the interleaved loop and the last one behind it
   auto sums_half = [&](const f32x16& z, int half, int t) BM_LAMBDA {
     float csum = 0.0f;
 #pragma unroll
@@ -1174,9 +1174,15 @@ __global__ void __launch_bounds__(256) score_reduce_kernel(PrefillArgs a, int pt
 // Workgroups per position tile.  A launch of fewer workgroups than compute units
 // takes as long as one of them, and sweep 2 is a third of that: idle units take
 // over its tiles, each after a sweep 1 of its own (every one needs the rows'
-// normalisers).  Sums and outputs stay the same bit for bit.  Per prompt, block by
-// block: 64 workgroups of b=1 s=4096 529 -> 457 us, 80 of b=5 d=64 s=1999 550 -> 484,
-// 8 of float32 b=2 s=512 (with 32 decode steps) 409 -> 375.  With a second
+// normalisers).  Sums and outputs stay the same bit for bit.  us a prompt, block by
+// block, with one workgroup per tile -> with those of this rule:
+//   workgroups (one per tile)       64 (4)     84-88 (3, 2)  104 (2)    128 (2)
+//   bf16 d=128 G=4 s=4096           514 -> 444 524 -> 453    524 -> 460 531 -> 470
+//   bf16 d=128 G=1 s=4096, B=512    449 -> 371 452 -> 386    454 -> 392 456 -> 398
+//   bf16 d=64 G=2 s=1999, B=100     453 -> 385 458 -> 408    462 -> 410 465 -> 415
+//   float32 d=64 G=1 s=512, B=64    244 -> 208 248 -> 224    249 -> 226 251 -> 228
+//   float32 d=128 G=4 s=1024, B=128 695 -> 587 699 -> 605    703 -> 615 709 -> 626
+// and 32 workgroups of the first 513 -> 435, 8 of the fourth 234 -> 195.  With a second
 // workgroup on a compute unit the repeated sweep 1 would cost time again (a wave's
 // tile takes half as long again beside another's), and past four the outputs'
 // store is as long as the sums.

@@ -10,7 +10,9 @@ for the last block: where each workgroup's time goes (prologue, the two
 sweeps, the step between them), how the prologue splits (query loads, tile
 copies, the wait), and the time spent issuing copies, waiting for them and in
 barriers inside the tile loops.  Tick length is calibrated against HIP events
-around the same launch.
+around the same launch.  The timeline build gives every position tile one
+workgroup: it does not show a small launch of the ordinary build, whose tiles
+are shared by up to four.
 
 The second form uses the ordinary library and fits the prefill time per step
 against the key tiles per workgroup over cache bounds 128 to 3072 (same
