@@ -709,14 +709,14 @@ __global__ void __launch_bounds__(kThreads, (BF16 || D == 64) ? 2 : 1) prefill_a
   // softmax's VALU work and the operands' LDS reads; two waves per SIMD cover each
   // other's phases only in part (b=64 s=4096, bound 512: counters put the matrix pipe
   // at 40% of a launch's cycles, 30% with the phases one after the other, and the clock
-  // at 2.0 of 2.4 GHz; a tile of this sweep takes 1.92 us of two workgroups' time, 2.16
-  // before).  So the order is pinned, MFMA by MFMA: the QK MFMAs with 24 of a lane's 32 logits between them, then the PV
-  // MFMAs with the last 8 and the maximum of zn.  VALU work is staged over three
-  // places (x = logit - reference, e = exp2, sum and pack), so that no
-  // instruction waits for the one before it; operand reads go out kAhead MFMAs
-  // early.  Sums keep the order of exp_tile.  Per prompt, with the copies' shared
-  // LDS base: full cache b=4 s=8192 2702 -> 2582 us, b=1 s=4096 556 -> 528 us,
-  // b=256 s=2048 (power-bound) 2% faster.
+  // at 2.0 of 2.4 GHz; a tile of this sweep takes 1.92 us with two workgroups on a
+  // compute unit, 2.16 before).  So the order is pinned, MFMA by MFMA: the QK MFMAs
+  // with 24 of a lane's 32 logits between them, then the PV MFMAs with the last 8
+  // and the maximum of zn.  VALU work is staged over three places (x = logit -
+  // reference, e = exp2, sum and pack), so that no instruction waits for the one
+  // before it; operand reads go out kAhead MFMAs early.  Sums keep the order of
+  // exp_tile.  Per prompt, with the copies' shared LDS base: full cache b=4 s=8192
+  // 2702 -> 2582 us, b=1 s=4096 556 -> 528 us, b=256 s=2048 2% faster.
   auto interleaved_step = [&](f32x16 (&zn)[2], const f32x16 (&zo)[2], uint32_t (&ka)[C::QSTEPS],
                               uint32_t (&va)[C::MT]) BM_LAMBDA {
     if constexpr (FAST) {
