@@ -276,8 +276,8 @@ def _cut_us(units, n, removed):
 
 def test_time_of_large_cuts_grows_with_their_entries():
     # the same moves with twice the entries to rank: the latter is reading twice the
-    # scores, not waiting for a place on a compute unit (2.7 times the time when one
-    # workgroup of the larger cut took a unit's LDS; 1.4 when it does not)
+    # scores, not waiting for a place on a compute unit (2.3 to 2.4 times the time when
+    # one workgroup of the larger cut took a unit's LDS; 1.4 to 1.5 now, six runs each)
     _need_gpu()
     t1, t2 = _cut_us(2048, 2048, 32), _cut_us(2048, 4096, 32)
     print(f"[select] 2048 units, 32 removed: {t1:.1f} us of 2048 entries, {t2:.1f} us of 4096", flush=True)
